@@ -1,9 +1,11 @@
 // Dense bf16 projection Y = X W^T (+ R) for the stacked-layer transition F,
 // with W in the linear-layer layout [n][k]: fp32 accumulation on
 // v_mfma_f32_16x16x32_bf16 (k in slices of 32 from 0) and one
-// round-to-nearest-even store.  Products with at least 256 tiles of
-// 256 x 256 (and K a multiple of 64) run the one-wave-per-SIMD kernel of
-// gemm_bf16_wide.hip; this register-staged kernel takes every other product.
+// round-to-nearest-even store.  Products with K a multiple of 128 run the
+// global->LDS kernels of gemm_bf16_dma.hip, those with at least 256 tiles of
+// 256 x 256 and K a multiple of 64 the one-wave-per-SIMD kernel of
+// gemm_bf16_wide.hip (both need X and W on 16-byte boundaries); this
+// register-staged kernel takes every other product.
 //
 // A workgroup computes a BM x BN output tile with WGM x WGN waves, each wave a
 // (TM * 32) x (TN * 32) block as (2 TM) x (2 TN) 16 x 16 MFMA tiles: 128 x 128
@@ -18,7 +20,7 @@
 // writes.  Output tiles are numbered so that each XCD (workgroup id mod 8)
 // takes a contiguous run of them, walked in groups of 8 tile rows, and the
 // workgroups sharing an XCD's L2 share their X and W panels.  The K loop
-// never splits and both kernels run the same products in the same order, so
+// never splits and all kernels run the same products in the same order, so
 // each output element's accumulation order is fixed (rows of Y are bitwise
 // independent of which other rows share the launch).
 #include <hip/hip_runtime.h>
@@ -188,7 +190,12 @@ void launch_tiles(int m, int n, int k, const void* x, const void* w, const void*
 
 hipError_t launch_gemm_bf16(int m, int n, int k, const void* x, const void* w, const void* r,
                             void* y, hipStream_t s) {
-  if (gemm_bf16_wide_eligible(m, n, k)) return launch_gemm_bf16_wide(m, n, k, x, w, r, y, s);
+  // global->LDS loads move 16 bytes a lane: X and W on 16-byte boundaries (a
+  // view into a larger tensor need not be), rows are (K a multiple of 8)
+  if ((((uintptr_t)x | (uintptr_t)w) & 15) == 0) {
+    if (gemm_bf16_dma_eligible(m, n, k)) return launch_gemm_bf16_dma(m, n, k, x, w, r, y, s);
+    if (gemm_bf16_wide_eligible(m, n, k)) return launch_gemm_bf16_wide(m, n, k, x, w, r, y, s);
+  }
   const int64_t tiles128 = (int64_t)((m + 127) / 128) * ((n + 127) / 128);
   if (tiles128 < 128) {
     // 128 x 128 tiles would leave most CUs idle (few rows: a short replayed

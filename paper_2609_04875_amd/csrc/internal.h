@@ -287,6 +287,12 @@ int replay_prefill_ws(pgsr_pool* p, int32_t layer, int32_t n, const int32_t* seq
 
 hipError_t launch_gemm_bf16(int m, int n, int k, const void* x, const void* w, const void* r,
                             void* y, hipStream_t s);
+// Global->LDS tiles from 16 x 16 to 256 x 128, or the 256 x 256 kernel, chosen
+// by a cost model (K a multiple of 128, m*k and n*k below 2^31, x and w on
+// 16-byte boundaries); same bits as above.
+bool gemm_bf16_dma_eligible(int m, int n, int k);
+hipError_t launch_gemm_bf16_dma(int m, int n, int k, const void* x, const void* w, const void* r, void* y,
+                                hipStream_t s);
 // One wave per SIMD, global->LDS tiles (products with at least 256 tiles of
 // 256 x 256, K a multiple of 64, m*k and n*k below 2^31); same bits as above.
 bool gemm_bf16_wide_eligible(int m, int n, int k);

@@ -92,6 +92,26 @@ def test_gemm_narrow_tiles_agree_bitwise(rows):
     assert torch.equal(part, full[a:b])
 
 
+@pytest.mark.parametrize("m,n,k,res", [
+    # one product per global->LDS tile (16 x 16, 32 x 16, 32 x 32, 64 x 32, 64 x 64, 128 x 64, 128 x 128,
+    # 256 x 128), with a ragged last tile in M or N; one K stage, fewer than the ring holds, and one more
+    (1, 4096, 128, False), (16, 4104, 1024, True), (17, 4096, 512, True), (33, 4096, 640, False),
+    (70, 4088, 1152, True), (200, 4096, 384, True), (300, 4096, 896, True), (700, 4104, 576 * 2, True),
+    (1400, 4096, 128, False), (1399, 4096, 448 * 2, True)])
+def test_gemm_global_to_lds_tiles_agree_bitwise(m, n, k, res):
+    """The global->LDS tiles against the register-staged kernel, which takes
+    the same product when X is not on a 16-byte boundary: same bits."""
+    from paper_2609_04875_amd import gemm_bf16
+    rng = np.random.default_rng(m + k)
+    x = _bf16_dev(rng.standard_normal((m, k)))
+    w = _bf16_dev(rng.standard_normal((n, k)) / np.sqrt(k))
+    r = _bf16_dev(rng.standard_normal((m, n))) if res else None
+    shifted = torch.empty(m * k + 4, dtype=torch.bfloat16, device="cuda")[4:].view(m, k)
+    shifted.copy_(x)
+    assert shifted.data_ptr() % 16 == 8 and x.data_ptr() % 16 == 0
+    assert torch.equal(gemm_bf16(x, w, r=r), gemm_bf16(shifted, w, r=r))
+
+
 @pytest.mark.parametrize("m,n,k", [(64, 128, 256), (4096, 4096, 128)])   # both kernels
 def test_gemm_residual_may_alias_output(m, n, k):
     from paper_2609_04875_amd import gemm_bf16
