@@ -316,6 +316,25 @@ int pgsr_gemm_bf16(int32_t m, int32_t n, int32_t k, const void *x, const void *w
                    const void *r, void *y, void *stream);
 
 /*
+ * The same products for up to three weights that share X (a layer's Q, K and V
+ * projections): Y_i = X W_i^T, the bits of `count` pgsr_gemm_bf16 calls, in
+ * one launch where that is the faster way.  n, w and y are host arrays of
+ * `count` (1 to 3) sizes and device pointers.
+ */
+int pgsr_gemm_bf16_multi(int32_t m, int32_t k, int32_t count, const int32_t *n, const void *x,
+                         const void *const *w, void *const *y, void *stream);
+
+/*
+ * Gate|up projection and SwiGLU gate: out[m][d_ff] = SiLU(X Wg^T) * (X Wu^T)
+ * with w [2 d_ff][k] (gate rows, then up rows), the bits of pgsr_gemm_bf16 into
+ * gate_up followed by pgsr_silu_mul_bf16 (both projections are rounded to bf16
+ * first).  gate_up [m][2 d_ff] is scratch: written only where the two steps
+ * run as two launches.
+ */
+int pgsr_gemm_silu_bf16(int32_t m, int32_t d_ff, int32_t k, const void *x, const void *w, void *gate_up,
+                        void *out, void *stream);
+
+/*
  * Elementwise steps of a full decoder layer around the projections (F of
  * Eq. (1) at the real geometries; the layer itself follows the public
  * architecture of the model families the paper runs).  bf16 device arrays,

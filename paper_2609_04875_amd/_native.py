@@ -24,7 +24,7 @@ EXPORTS = (
     "pgsr_pool_refresh", "pgsr_seq_len", "pgsr_free_blocks", "pgsr_workspace_bytes",
     "pgsr_kv_crop", "pgsr_kv_fork", "pgsr_replay_prefill", "pgsr_replay_prefill_static",
     "pgsr_restore_replay_prefill",
-    "pgsr_full_reset_prefill", "pgsr_gemm_bf16",
+    "pgsr_full_reset_prefill", "pgsr_gemm_bf16", "pgsr_gemm_bf16_multi", "pgsr_gemm_silu_bf16",
     "pgsr_pool_enable_timing", "pgsr_pool_last_times", "pgsr_pool_set_kv_scales",
     "pgsr_pool_set_prefill_kernel", "pgsr_pool_set_clock_buffer", "pgsr_pool_last_clock",
     "pgsr_graph_create", "pgsr_graph_destroy", "pgsr_graph_append", "pgsr_graph_size",
@@ -108,6 +108,10 @@ def _load() -> ctypes.CDLL:
     lib.pgsr_pool_set_prefill_kernel.argtypes = [P, ctypes.c_int]
     lib.pgsr_gemm_bf16.restype = ctypes.c_int
     lib.pgsr_gemm_bf16.argtypes = [i32, i32, i32, P, P, P, P, P]
+    lib.pgsr_gemm_bf16_multi.restype = ctypes.c_int
+    lib.pgsr_gemm_bf16_multi.argtypes = [i32, i32, i32, P, P, P, P, P]
+    lib.pgsr_gemm_silu_bf16.restype = ctypes.c_int
+    lib.pgsr_gemm_silu_bf16.argtypes = [i32, i32, i32, P, P, P, P, P]
     lib.pgsr_sample_workspace_bytes.restype = ctypes.c_size_t
     lib.pgsr_sample_workspace_bytes.argtypes = [i32, i32]
     lib.pgsr_sample_tokens.restype = ctypes.c_int

@@ -33,6 +33,7 @@
 #include <cmath>
 #include <utility>
 
+#include "elementwise.h"
 #include "internal.h"
 
 // The requests write M0 (the LDS address of a global->LDS load) from inline
@@ -52,8 +53,6 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 constexpr int kSub = 64;               // k per image row (128 bytes)
 constexpr int kCus = 256;
 
-__device__ inline float bf16_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
-
 template <class F, int... I>
 __device__ __forceinline__ void static_for(F&& f, std::integer_sequence<int, I...>) {
   (f(std::integral_constant<int, I>{}), ...);
@@ -68,10 +67,23 @@ __device__ __forceinline__ void wait_loads() {
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
 }
 
-template <int BM, int BN, int WGM, int WGN, int KSUB, int NST, int GS, int WPE, int GM>
-__global__ void __launch_bounds__(WGM * WGN * 64, WPE)
-gemm_bf16_dma_kernel(int M, int N, int K, const uint16_t* __restrict__ X, const uint16_t* __restrict__ W,
-                     const uint16_t* R, uint16_t* Y) {
+// Up to three products of the same X (W_s of n_s rows, Y_s [M][n_s]); their
+// tile columns are numbered through.
+struct DmaArgs {
+  int m, k, count;
+  const uint16_t* x;
+  const uint16_t* w[kGemmMulti];
+  const uint16_t* r[kGemmMulti];
+  uint16_t* y[kGemmMulti];
+  int n[kGemmMulti];
+};
+
+// SILU: W holds n gate rows, then n up rows; a tile takes BN / 2 of each in
+// alternating groups of 16, so a lane holds gate and up of the same outputs
+// (sub-tiles 2 i and 2 i + 1) and stores bf16(SiLU(bf16(gate)) * bf16(up)),
+// the bits of the projection followed by the gated product.
+template <int BM, int BN, int WGM, int WGN, int KSUB, int NST, int GS, int GM, bool SILU>
+__global__ void __launch_bounds__(WGM * WGN * 64, 1) gemm_bf16_dma_kernel(DmaArgs a) {
   constexpr int NW = WGM * WGN;
   constexpr int TM = BM / WGM / 16, TN = BN / WGN / 16;
   constexpr int XR = BM / 8 / NW, WR = BN / 8 / NW;       // 1 KB runs per wave and sub-image
@@ -87,14 +99,35 @@ gemm_bf16_dma_kernel(int M, int N, int K, const uint16_t* __restrict__ X, const 
   // output tile of this workgroup: XCD x = blockIdx % 8 takes tiles
   // [x * per_xcd, (x + 1) * per_xcd), in groups of GM tile rows (the tile rows
   // of one W panel run side by side on one XCD, so its L2 takes W once)
-  const int n_tm = (M + BM - 1) / BM, n_tn = (N + BN - 1) / BN;
+  constexpr int BNO = SILU ? BN / 2 : BN;                  // output columns of a tile
+  const int M = a.m, K = a.k;
+  const int n_tm = (M + BM - 1) / BM;
+  int n_tn = 0;
+#pragma unroll
+  for (int i = 0; i < kGemmMulti; ++i) n_tn += i < a.count ? (a.n[i] + BNO - 1) / BNO : 0;
   const int per_xcd = (n_tm * n_tn + 7) / 8;
   const int t = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
   if (t >= n_tm * n_tn) return;
   const int grp = t / (GM * n_tn), first_m = grp * GM;
   const int gsize = min(n_tm - first_m, GM);
   const int idx = t - grp * GM * n_tn;
-  const int m0 = (first_m + idx % gsize) * BM, n0 = (idx / gsize) * BN;
+  const int m0 = (first_m + idx % gsize) * BM;
+  int tn = idx / gsize;
+  const uint16_t* __restrict__ X = a.x;
+  const uint16_t* __restrict__ W = a.w[0];
+  const uint16_t* R = a.r[0];
+  uint16_t* Y = a.y[0];
+  int N = a.n[0];
+#pragma unroll
+  for (int i = 1; i < kGemmMulti; ++i)
+    if (i < a.count && tn >= (N + BNO - 1) / BNO) {
+      tn -= (N + BNO - 1) / BNO;
+      W = a.w[i];
+      R = a.r[i];
+      Y = a.y[i];
+      N = a.n[i];
+    }
+  const int n0 = tn * BNO;
 
   const int tid = threadIdx.x;
   const int w = NW == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -112,7 +145,8 @@ gemm_bf16_dma_kernel(int M, int N, int K, const uint16_t* __restrict__ X, const 
 #pragma unroll
   for (int j = 0; j < WR; ++j) {
     const int row = 8 * (w + NW * j) + lane / 8;
-    woff[j] = 2u * ((uint32_t)min(n0 + row, N - 1) * (uint32_t)K + 8u * ((lane & 7) ^ gsw(row)));
+    const int wrow = SILU ? min(n0 + (row >> 5) * 16 + (row & 15), N - 1) + ((row >> 4) & 1) * N : min(n0 + row, N - 1);
+    woff[j] = 2u * ((uint32_t)wrow * (uint32_t)K + 8u * ((lane & 7) ^ gsw(row)));
   }
   const uint32_t lds0 = (uint32_t)(uintptr_t)&lds[0] + 1024u * w;
   const int nst = K / (kSub * KSUB);
@@ -213,30 +247,46 @@ gemm_bf16_dma_kernel(int M, int N, int K, const uint16_t* __restrict__ X, const 
   for (int j = 0; j < TM; ++j) {
     const int m = m0 + wm + 16 * j + r16;
     if (m >= M) continue;
+    if constexpr (SILU) {
 #pragma unroll
-    for (int i = 0; i < TN; ++i) {
-      const int n = n0 + wn + 16 * i + 4 * g4;
-      if (n >= N) continue;                        // N is a multiple of 8: whole group in or out
-      const int64_t o = (int64_t)m * N + n;
-      f32x4 v = acc[i][j];
-      if (R) {
-        const u32x2 rb = *(const u32x2*)(R + o);
-        v[0] += bf16_to_f32((uint16_t)(rb[0] & 0xFFFF));
-        v[1] += bf16_to_f32((uint16_t)(rb[0] >> 16));
-        v[2] += bf16_to_f32((uint16_t)(rb[1] & 0xFFFF));
-        v[3] += bf16_to_f32((uint16_t)(rb[1] >> 16));
+      for (int i = 0; i < TN; i += 2) {
+        const int n = n0 + wn / 2 + 8 * i + 4 * g4;
+        if (n >= N) continue;                      // N is a multiple of 8: whole group in or out
+        const bf16x4 gate = __builtin_convertvector(acc[i][j], bf16x4);
+        const bf16x4 up = __builtin_convertvector(acc[i + 1][j], bf16x4);
+        uint32_t o[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) o[q] = f32_to_bf16(silu_f32((float)gate[q]) * (float)up[q]);
+        *(u32x2*)(Y + (int64_t)m * N + n) = u32x2{o[0] | (o[1] << 16), o[2] | (o[3] << 16)};
       }
-      *(bf16x4*)(Y + o) = __builtin_convertvector(v, bf16x4);
+    } else {
+#pragma unroll
+      for (int i = 0; i < TN; ++i) {
+        const int n = n0 + wn + 16 * i + 4 * g4;
+        if (n >= N) continue;                      // N is a multiple of 8: whole group in or out
+        const int64_t o = (int64_t)m * N + n;
+        f32x4 v = acc[i][j];
+        if (R) {
+          const u32x2 rb = *(const u32x2*)(R + o);
+          v[0] += lo_bf16(rb[0]);
+          v[1] += hi_bf16(rb[0]);
+          v[2] += lo_bf16(rb[1]);
+          v[3] += hi_bf16(rb[1]);
+        }
+        *(bf16x4*)(Y + o) = __builtin_convertvector(v, bf16x4);
+      }
     }
   }
 }
 
-template <int BM, int BN, int WGM, int WGN, int KSUB, int NST, int GS, int WPE, int GM>
-void launch_dma(int m, int n, int k, const void* x, const void* w, const void* r, void* y, hipStream_t s) {
-  const int tiles = ((m + BM - 1) / BM) * ((n + BN - 1) / BN);
-  hipLaunchKernelGGL((gemm_bf16_dma_kernel<BM, BN, WGM, WGN, KSUB, NST, GS, WPE, GM>), dim3(8 * ((tiles + 7) / 8)),
-                     dim3(WGM * WGN * 64), 0, s, m, n, k, (const uint16_t*)x, (const uint16_t*)w,
-                     (const uint16_t*)r, (uint16_t*)y);
+template <int BM, int BN, int WGM, int WGN, int KSUB, int NST, int GS, int GM, bool SILU = false>
+void launch_dma(const DmaArgs& a, hipStream_t s) {
+  constexpr int BNO = SILU ? BN / 2 : BN;
+  int cols = 0;
+  for (int i = 0; i < a.count; ++i) cols += (a.n[i] + BNO - 1) / BNO;
+  const int tiles = ((a.m + BM - 1) / BM) * cols;
+  hipLaunchKernelGGL((gemm_bf16_dma_kernel<BM, BN, WGM, WGN, KSUB, NST, GS, GM, SILU>), dim3(8 * ((tiles + 7) / 8)),
+                     dim3(WGM * WGN * 64), 0, s, a);
 }
 
 // Tile choice: the time of a launch is close to
@@ -254,15 +304,17 @@ constexpr TileCost kTiles[] = {{16, 16, 68},  {32, 16, 112},  {32, 32, 122},  {6
                                {128, 64, 350}, {128, 128, 538}, {256, 128, 885}, {256, 256, 1450}};
 constexpr int kWide = 8;
 
-int pick_tile(int m, int n, int k, bool wide_ok) {
-  int best = 0;
+// the cheapest of tiles lo .. hi for the given products of one X
+int pick_tile(int m, int count, const int* n, int lo, int hi) {
+  int best = lo;
   double best_cost = 0;
-  for (int i = 0; i <= kWide; ++i) {
-    if (i == kWide && !wide_ok) break;
+  for (int i = lo; i <= hi; ++i) {
     const TileCost& t = kTiles[i];
-    const double r = (double)((m + t.bm - 1) / t.bm) * ((n + t.bn - 1) / t.bn) / kCus;
+    double cols = 0;
+    for (int j = 0; j < count; ++j) cols += (n[j] + t.bn - 1) / t.bn;
+    const double r = (double)((m + t.bm - 1) / t.bm) * cols / kCus;
     const double cost = t.step_ns * (r <= 1.0 ? 1.0 : 0.36 * r + 0.64 * ceil(r));
-    if (i == 0 || cost < best_cost) {
+    if (i == lo || cost < best_cost) {
       best = i;
       best_cost = cost;
     }
@@ -276,19 +328,89 @@ bool gemm_bf16_dma_eligible(int m, int n, int k) {
   return k >= 128 && k % 128 == 0 && (int64_t)m * k < ((int64_t)1 << 31) && (int64_t)n * k < ((int64_t)1 << 31);
 }
 
+static hipError_t run_tile(int tile, const DmaArgs& a, hipStream_t s) {
+  switch (tile) {
+    case 0: launch_dma<16, 16, 1, 1, 2, 8, 4, 8>(a, s); break;
+    case 1: launch_dma<32, 16, 2, 1, 2, 8, 4, 8>(a, s); break;
+    case 2: launch_dma<32, 32, 2, 2, 2, 4, 4, 8>(a, s); break;
+    case 3: launch_dma<64, 32, 2, 2, 2, 6, 2, 8>(a, s); break;
+    case 4: launch_dma<64, 64, 2, 2, 2, 4, 2, 8>(a, s); break;
+    case 5: launch_dma<128, 64, 4, 2, 2, 3, 2, 8>(a, s); break;
+    case 6: launch_dma<128, 128, 4, 2, 1, 4, 1, 8>(a, s); break;
+    case 7: launch_dma<256, 128, 4, 2, 1, 3, 1, 4>(a, s); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
 hipError_t launch_gemm_bf16_dma(int m, int n, int k, const void* x, const void* w, const void* r, void* y,
                                 hipStream_t s) {
   if (!gemm_bf16_dma_eligible(m, n, k)) return hipErrorInvalidValue;
-  switch (pick_tile(m, n, k, gemm_bf16_wide_eligible(m, n, k))) {
-    case 0: launch_dma<16, 16, 1, 1, 2, 8, 4, 1, 8>(m, n, k, x, w, r, y, s); break;
-    case 1: launch_dma<32, 16, 2, 1, 2, 8, 4, 1, 8>(m, n, k, x, w, r, y, s); break;
-    case 2: launch_dma<32, 32, 2, 2, 2, 4, 4, 1, 8>(m, n, k, x, w, r, y, s); break;
-    case 3: launch_dma<64, 32, 2, 2, 2, 6, 2, 1, 8>(m, n, k, x, w, r, y, s); break;
-    case 4: launch_dma<64, 64, 2, 2, 2, 4, 2, 1, 8>(m, n, k, x, w, r, y, s); break;
-    case 5: launch_dma<128, 64, 4, 2, 2, 3, 2, 1, 8>(m, n, k, x, w, r, y, s); break;
-    case 6: launch_dma<128, 128, 4, 2, 1, 4, 1, 1, 8>(m, n, k, x, w, r, y, s); break;
-    case 7: launch_dma<256, 128, 4, 2, 1, 3, 1, 1, 4>(m, n, k, x, w, r, y, s); break;
-    default: return launch_gemm_bf16_wide(m, n, k, x, w, r, y, s);
+  const int tile = pick_tile(m, 1, &n, 0, gemm_bf16_wide_eligible(m, n, k) ? kWide : kWide - 1);
+  if (tile == kWide) return launch_gemm_bf16_wide(m, n, k, x, w, r, y, s);
+  DmaArgs a{m, k, 1, (const uint16_t*)x, {(const uint16_t*)w}, {(const uint16_t*)r}, {(uint16_t*)y}, {n}};
+  return run_tile(tile, a, s);
+}
+
+// One launch for the products unless the 256 x 256 kernel is the better one
+// for them together: a launch less for each, and the short ones (n = 1024: 64
+// tiles of 16 columns) fill the chip beside the long one (1 token x
+// (4096 + 1024 + 1024) x 4096: 11.0 against 7.8 + 7.1 + 7.1 us, 102 tokens:
+// 19.1 against 13.7 + 8.0 + 8.0 us).
+bool gemm_bf16_multi_eligible(int m, int k, int count, const int* n) {
+  if (count < 1 || count > kGemmMulti) return false;
+  int64_t total = 0;
+  for (int i = 0; i < count; ++i) {
+    if (!gemm_bf16_dma_eligible(m, n[i], k)) return false;
+    total += n[i];
+  }
+  if (total > INT32_MAX) return false;
+  const int sum = (int)total;
+  return !(gemm_bf16_wide_eligible(m, sum, k) && pick_tile(m, 1, &sum, 0, kWide) == kWide);
+}
+
+hipError_t launch_gemm_bf16_multi(int m, int k, int count, const int* n, const void* x, const void* const* w,
+                                  void* const* y, hipStream_t s) {
+  if (!gemm_bf16_multi_eligible(m, k, count, n)) return hipErrorInvalidValue;
+  DmaArgs a{};
+  a.m = m;
+  a.k = k;
+  a.count = count;
+  a.x = (const uint16_t*)x;
+  for (int i = 0; i < count; ++i) {
+    a.w[i] = (const uint16_t*)w[i];
+    a.y[i] = (uint16_t*)y[i];
+    a.n[i] = n[i];
+  }
+  return run_tile(pick_tile(m, count, n, 0, kWide - 1), a, s);
+}
+
+// Gate|up projection with the gated product in the epilogue.  Two sub-tiles of
+// 16 columns per wave are the least that hold a gate and an up group, so the
+// narrowest tiles differ from those above.  The 256 x 256 kernel has no such
+// epilogue: where it would be chosen the two launches stay.
+bool gemm_bf16_silu_eligible(int m, int dff, int k) {
+  if (dff % 8 != 0 || dff > (1 << 30) || !gemm_bf16_dma_eligible(m, 2 * dff, k)) return false;
+  const int n = 2 * dff;
+  return pick_tile(m, 1, &n, 0, gemm_bf16_wide_eligible(m, n, k) ? kWide : kWide - 1) != kWide;
+}
+
+hipError_t launch_gemm_bf16_silu(int m, int dff, int k, const void* x, const void* w, void* y, hipStream_t s) {
+  if (!gemm_bf16_silu_eligible(m, dff, k)) return hipErrorInvalidValue;
+  DmaArgs a{m, k, 1, (const uint16_t*)x, {(const uint16_t*)w}, {nullptr}, {(uint16_t*)y}, {dff}};
+  const int n = 2 * dff;
+  switch (pick_tile(m, 1, &n, 0, kWide - 1)) {
+    case 0: launch_dma<16, 32, 1, 1, 2, 5, 2, 8, true>(a, s); break;
+    case 1:
+    case 2:
+      if (m <= 16) launch_dma<16, 32, 1, 1, 2, 5, 2, 8, true>(a, s);
+      else launch_dma<32, 32, 2, 1, 2, 4, 4, 8, true>(a, s);
+      break;
+    case 3: launch_dma<64, 32, 4, 1, 2, 6, 2, 8, true>(a, s); break;
+    case 4: launch_dma<64, 64, 2, 2, 2, 4, 2, 8, true>(a, s); break;
+    case 5: launch_dma<128, 64, 4, 2, 2, 3, 2, 8, true>(a, s); break;
+    case 6: launch_dma<128, 128, 4, 2, 1, 4, 1, 8, true>(a, s); break;
+    default: launch_dma<256, 128, 4, 2, 1, 3, 1, 4, true>(a, s); break;
   }
   return hipGetLastError();
 }

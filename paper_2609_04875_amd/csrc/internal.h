@@ -293,6 +293,16 @@ hipError_t launch_gemm_bf16(int m, int n, int k, const void* x, const void* w, c
 bool gemm_bf16_dma_eligible(int m, int n, int k);
 hipError_t launch_gemm_bf16_dma(int m, int n, int k, const void* x, const void* w, const void* r, void* y,
                                 hipStream_t s);
+// Up to kGemmMulti products of the same X in one launch, and the gate|up
+// projection with the gated product in its epilogue (w [2 dff][k], y [m][dff]);
+// the bits of the separate calls.  False where separate launches are better
+// or needed.
+constexpr int kGemmMulti = 3;
+bool gemm_bf16_multi_eligible(int m, int k, int count, const int* n);
+hipError_t launch_gemm_bf16_multi(int m, int k, int count, const int* n, const void* x, const void* const* w,
+                                  void* const* y, hipStream_t s);
+bool gemm_bf16_silu_eligible(int m, int dff, int k);
+hipError_t launch_gemm_bf16_silu(int m, int dff, int k, const void* x, const void* w, void* y, hipStream_t s);
 // One wave per SIMD, global->LDS tiles (products with at least 256 tiles of
 // 256 x 256, K a multiple of 64, m*k and n*k below 2^31); same bits as above.
 bool gemm_bf16_wide_eligible(int m, int n, int k);

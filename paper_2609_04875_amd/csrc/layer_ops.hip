@@ -7,6 +7,7 @@
 
 #include <cstdint>
 
+#include "elementwise.h"
 #include "internal.h"
 
 namespace pgsr {
@@ -15,16 +16,7 @@ namespace {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-__device__ inline float lo_bf16(uint32_t w) { return __uint_as_float(w << 16); }
-__device__ inline float hi_bf16(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
-
-// fp32 -> bf16 bits, round to nearest even (finite inputs; NaN stays NaN).
-__device__ inline uint32_t to_bf16(float f) {
-  const uint32_t u = __float_as_uint(f);
-  if ((u & 0x7F800000u) == 0x7F800000u) return (u >> 16) | ((u & 0xFFFFu) ? 0x40u : 0u);
-  return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
-}
-__device__ inline uint32_t pack(float a, float b) { return to_bf16(a) | (to_bf16(b) << 16); }
+__device__ inline uint32_t pack(float a, float b) { return f32_to_bf16(a) | (f32_to_bf16(b) << 16); }
 
 constexpr int kThreads = 256;
 
@@ -86,8 +78,8 @@ __global__ void __launch_bounds__(kThreads) rope_kernel(int64_t n_pairs, int32_t
     uint16_t* row = x + th * d;
     const float a = __uint_as_float((uint32_t)row[i] << 16);
     const float b = __uint_as_float((uint32_t)row[i + half] << 16);
-    row[i] = (uint16_t)to_bf16(a * c - b * s);
-    row[i + half] = (uint16_t)to_bf16(b * c + a * s);
+    row[i] = (uint16_t)f32_to_bf16(a * c - b * s);
+    row[i + half] = (uint16_t)f32_to_bf16(b * c + a * s);
   }
 }
 
@@ -106,8 +98,7 @@ __global__ void __launch_bounds__(kThreads) silu_mul_kernel(int64_t n_chunks, in
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const float g0 = lo_bf16(g[k]), g1 = hi_bf16(g[k]);
-      const float s0 = g0 / (1.f + expf(-g0)), s1 = g1 / (1.f + expf(-g1));
-      o[k] = pack(s0 * lo_bf16(u[k]), s1 * hi_bf16(u[k]));
+      o[k] = pack(silu_f32(g0) * lo_bf16(u[k]), silu_f32(g1) * hi_bf16(u[k]));
     }
     *(u32x4*)(out + r * dff + j) = o;
   }

@@ -1045,6 +1045,51 @@ int pgsr_gemm_bf16(int32_t m, int32_t n, int32_t k, const void* x, const void* w
   return ok();
 }
 
+static bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
+
+int pgsr_gemm_bf16_multi(int32_t m, int32_t k, int32_t count, const int32_t* n, const void* x,
+                         const void* const* w, void* const* y, void* stream) {
+  if (count < 1 || count > kGemmMulti) return fail(PGSR_EINVAL, "count = %d (1 to %d)", count, kGemmMulti);
+  if (!n || !w || !y) return fail(PGSR_EINVAL, "null array");
+  if (m < 0 || k < 0) return fail(PGSR_EINVAL, "negative size");
+  if (k % 8) return fail(PGSR_EUNSUPPORTED, "n and k must be multiples of 8");
+  bool one = aligned16(x);
+  for (int32_t i = 0; i < count; ++i) {
+    if (n[i] < 0) return fail(PGSR_EINVAL, "negative size");
+    if (n[i] % 8) return fail(PGSR_EUNSUPPORTED, "n and k must be multiples of 8");
+    if (m > 0 && n[i] > 0 && (!x || !w[i] || !y[i])) return fail(PGSR_EINVAL, "null pointer");
+    one = one && n[i] > 0 && aligned16(w[i]);
+  }
+  if (m == 0) return ok();
+  hipStream_t st = (hipStream_t)stream;
+  hipError_t err = hipSuccess;
+  if (one && gemm_bf16_multi_eligible(m, k, count, n)) {
+    err = launch_gemm_bf16_multi(m, k, count, n, x, w, y, st);
+  } else {
+    for (int32_t i = 0; i < count && err == hipSuccess; ++i)
+      if (n[i] > 0) err = launch_gemm_bf16(m, n[i], k, x, w[i], nullptr, y[i], st);
+  }
+  return err == hipSuccess ? ok() : hip_fail(err, "gemm launch");
+}
+
+int pgsr_gemm_silu_bf16(int32_t m, int32_t d_ff, int32_t k, const void* x, const void* w, void* gate_up,
+                        void* out, void* stream) {
+  if (m < 0 || d_ff < 0 || k < 0) return fail(PGSR_EINVAL, "negative size");
+  if (d_ff % 8 || k % 8) return fail(PGSR_EUNSUPPORTED, "d_ff and k must be multiples of 8");
+  if (d_ff > INT32_MAX / 2) return fail(PGSR_ERANGE, "d_ff = %d", d_ff);
+  if (m == 0 || d_ff == 0) return ok();
+  if (!x || !w || !gate_up || !out) return fail(PGSR_EINVAL, "null pointer");
+  hipStream_t st = (hipStream_t)stream;
+  hipError_t err;
+  if (aligned16(x) && aligned16(w) && gemm_bf16_silu_eligible(m, d_ff, k)) {
+    err = launch_gemm_bf16_silu(m, d_ff, k, x, w, out, st);
+  } else {
+    err = launch_gemm_bf16(m, 2 * d_ff, k, x, w, nullptr, gate_up, st);
+    if (err == hipSuccess) err = launch_silu_mul(m, d_ff, gate_up, out, st);
+  }
+  return err == hipSuccess ? ok() : hip_fail(err, "gemm + silu launch");
+}
+
 // Vocabulary entries per sampling workgroup (a multiple of 4: Philox blocks
 // never straddle two chunks).
 constexpr int32_t kSampleChunk = 8192;

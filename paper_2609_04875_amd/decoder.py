@@ -15,7 +15,7 @@ from typing import Dict, List, Optional, Sequence
 import torch
 
 from . import _native as N
-from .pool import KVPool, gemm_bf16
+from .pool import KVPool, gemm_bf16, gemm_bf16_multi, gemm_silu_bf16
 
 
 def _stream(stream):
@@ -84,9 +84,7 @@ class DecoderReplay:
         last = len(self.w) - 1
         for li, w in enumerate(self.w):
             rmsnorm(x, w["g_attn"], self.eps, out=h)
-            gemm_bf16(h, w["wq"], out=q.view(n, -1))
-            gemm_bf16(h, w["wk"], out=k.view(n, -1))
-            gemm_bf16(h, w["wv"], out=v.view(n, -1))
+            gemm_bf16_multi(h, (w["wq"], w["wk"], w["wv"]), (q, k, v))
             rope_(q, pos, self.theta)
             rope_(k, pos, self.theta)
             rc = fn(li, [seq], [n], q, k, v, o, scale, commit=(li == last))
@@ -94,8 +92,7 @@ class DecoderReplay:
                 raise N.PgsrError(rc, N.lib.pgsr_last_error().decode())
             gemm_bf16(o, w["wo"], r=x, out=x)                 # x <- x + O Wo
             rmsnorm(x, w["g_mlp"], self.eps, out=h)
-            gemm_bf16(h, w["w_gate_up"], out=gu)
-            silu_mul(gu, out=a)
+            gemm_silu_bf16(h, w["w_gate_up"], gu, a)
             gemm_bf16(a, w["w_down"], r=x, out=x)             # x <- x + MLP(x)
         return x
 

@@ -254,3 +254,35 @@ def gemm_bf16(x: torch.Tensor, w: torch.Tensor, r: Optional[torch.Tensor] = None
                                  _dev_ptr(r, bf, "r", dv, m * n) if r is not None else None,
                                  _dev_ptr(out, bf, "out", dv, m * n), _stream_ptr(stream, dv)))
     return out
+
+
+def gemm_bf16_multi(x: torch.Tensor, ws: Sequence[torch.Tensor], outs: Sequence[torch.Tensor], stream=None):
+    """out_i = X W_i^T for up to three weights: the bits of one ``gemm_bf16``
+    each, in one launch where that is the faster way."""
+    m, k = x.shape
+    dv, bf, c = x.device.index, torch.bfloat16, len(ws)
+    if len(outs) != c:
+        raise ValueError(f"{c} weights but {len(outs)} outputs")
+    for w in ws:
+        if w.shape[1] != k:
+            raise ValueError("inner dimensions differ")
+    ns = (ctypes.c_int32 * c)(*(w.shape[0] for w in ws))
+    wp = (ctypes.c_void_p * c)(*(_dev_ptr(w, bf, "w", dv) for w in ws))
+    yp = (ctypes.c_void_p * c)(*(_dev_ptr(o, bf, "out", dv, m * n) for o, n in zip(outs, ns)))
+    N.check(N.lib.pgsr_gemm_bf16_multi(m, k, c, ns, _dev_ptr(x, bf, "x"), wp, yp, _stream_ptr(stream, dv)))
+    return outs
+
+
+def gemm_silu_bf16(x: torch.Tensor, w_gate_up: torch.Tensor, scratch: torch.Tensor, out: torch.Tensor, stream=None):
+    """out = SiLU(X Wg^T) * (X Wu^T), ``w_gate_up`` [2 d_ff, k] (gate rows, then
+    up rows): the bits of ``gemm_bf16`` followed by ``silu_mul``; ``scratch``
+    [m, 2 d_ff] is used where they run as two launches."""
+    m, k = x.shape
+    n2, k2 = w_gate_up.shape
+    if k2 != k or n2 % 2:
+        raise ValueError("w_gate_up must be [2 d_ff, k]")
+    dv, bf = x.device.index, torch.bfloat16
+    N.check(N.lib.pgsr_gemm_silu_bf16(m, n2 // 2, k, _dev_ptr(x, bf, "x"), _dev_ptr(w_gate_up, bf, "w", dv),
+                                      _dev_ptr(scratch, bf, "scratch", dv, m * n2),
+                                      _dev_ptr(out, bf, "out", dv, m * (n2 // 2)), _stream_ptr(stream, dv)))
+    return out

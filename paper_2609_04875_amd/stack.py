@@ -15,7 +15,7 @@ from typing import List, Optional, Sequence
 import torch
 
 from . import _native as N
-from .pool import KVPool, gemm_bf16
+from .pool import KVPool, gemm_bf16, gemm_bf16_multi
 
 
 class StackedReplay:
@@ -50,9 +50,7 @@ class StackedReplay:
         x = x.clone()
         last = len(self.w) - 1
         for li, (wq, wk, wv, wo) in enumerate(self.w):
-            gemm_bf16(x, wq, out=q)
-            gemm_bf16(x, wk, out=k)
-            gemm_bf16(x, wv, out=v)
+            gemm_bf16_multi(x, (wq, wk, wv), (q, k, v))
             rc = fn(li, [seq], [n], q, k, v, o, scale, commit=(li == last))
             if rc:
                 raise N.PgsrError(rc, N.lib.pgsr_last_error().decode())

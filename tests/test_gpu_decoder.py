@@ -12,7 +12,8 @@ from oracle import bf16_round
 from oracle import decoder as DEC
 from gpu_helpers import log
 
-from paper_2609_04875_amd import DecoderReplay, rmsnorm, rope_, silu_mul
+from paper_2609_04875_amd import DecoderReplay, gemm_bf16, rmsnorm, rope_, silu_mul
+from paper_2609_04875_amd.pool import gemm_bf16_multi, gemm_silu_bf16
 
 pytestmark = pytest.mark.gpu
 
@@ -73,6 +74,32 @@ def _dev_weights(ws):
     return [{"wq": _dev(w["wq"].T), "wk": _dev(w["wk"].T), "wv": _dev(w["wv"].T), "wo": _dev(w["wo"].T),
              "w_gate_up": _dev(np.concatenate([w["wg"].T, w["wu"].T])), "w_down": _dev(w["wd"].T),
              "g_attn": _dev(w["g_attn"]), "g_mlp": _dev(w["g_mlp"])} for w in ws]
+
+
+@pytest.mark.parametrize("m,dff,k", [
+    # one product per tile of the projection with the gate in its epilogue, ragged in rows or columns (a
+    # last group of 8), then K = 192 and the 256 x 256 kernel's size, which run as two launches
+    (1, 1000, 128), (16, 2048, 640), (17, 1024, 256), (40, 2040, 384), (100, 1496, 1024), (200, 3064, 384),
+    (300, 2048, 896), (700, 2056, 256), (1400, 2040, 128), (9, 96, 192), (4096, 2048, 128)])
+def test_projection_with_gate_equals_two_steps(m, dff, k):
+    rng = np.random.default_rng(m + dff)
+    x, w = _dev(rng.standard_normal((m, k)) * 2), _dev(rng.standard_normal((2 * dff, k)) * k ** -0.5)
+    want = silu_mul(gemm_bf16(x, w))
+    scratch, out = torch.empty(m, 2 * dff, dtype=torch.bfloat16, device="cuda"), torch.empty_like(want)
+    assert torch.equal(gemm_silu_bf16(x, w, scratch, out), want)
+
+
+@pytest.mark.parametrize("m,k,ns", [(1, 256, (512, 128, 128)), (40, 640, (1000, 8, 264)), (102, 384, (2048, 1024)),
+                                    (300, 128, (4096, 1024, 1024)), (33, 72, (64, 16, 24)),
+                                    (4096, 128, (4096, 64, 64)), (5, 128, (4104,))])
+def test_projections_in_one_call_equal_separate_ones(m, k, ns):
+    rng = np.random.default_rng(m + k)
+    x = _dev(rng.standard_normal((m, k)))
+    ws = [_dev(rng.standard_normal((n, k)) * k ** -0.5) for n in ns]
+    outs = [torch.empty(m, n, dtype=torch.bfloat16, device="cuda") for n in ns]
+    gemm_bf16_multi(x, ws, outs)
+    for w, o in zip(ws, outs):
+        assert torch.equal(o, gemm_bf16(x, w))
 
 
 @pytest.mark.parametrize("hq,hkv,d", [(4, 2, 64), (7, 1, 64)])
