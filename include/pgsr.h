@@ -354,6 +354,9 @@ int pgsr_rmsnorm_bf16(int32_t n, int32_t d_model, const void *x, const void *gai
  */
 int pgsr_rope_bf16(int32_t n, int32_t n_heads, int32_t head_dim, void *x, const int32_t *positions,
                    double theta, void *stream);
+/* The same on a layer's q [n][n_q_heads][head_dim] and k [n][n_kv_heads][head_dim], in one launch. */
+int pgsr_rope_qk_bf16(int32_t n, int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, void *q, void *k,
+                      const int32_t *positions, double theta, void *stream);
 /*
  * SwiGLU gate: out[r][j] = SiLU(gate_up[r][j]) * gate_up[r][d_ff + j] with
  * SiLU(g) = g / (1 + e^-g); gate_up [n][2 d_ff], out [n][d_ff], d_ff a

@@ -32,6 +32,7 @@ EXPORTS = (
     "pgsr_graph_taint_closure", "pgsr_graph_policy_boundaries", "pgsr_ckpt_create",
     "pgsr_ckpt_destroy", "pgsr_ckpt_register", "pgsr_ckpt_count", "pgsr_forget_plan_query",
     "pgsr_sample_workspace_bytes", "pgsr_sample_tokens", "pgsr_rmsnorm_bf16", "pgsr_rope_bf16",
+    "pgsr_rope_qk_bf16",
     "pgsr_silu_mul_bf16",
 )
 
@@ -121,6 +122,8 @@ def _load() -> ctypes.CDLL:
     lib.pgsr_rmsnorm_bf16.argtypes = [i32, i32, P, P, f32, P, P]
     lib.pgsr_rope_bf16.restype = ctypes.c_int
     lib.pgsr_rope_bf16.argtypes = [i32, i32, i32, P, P, ctypes.c_double, P]
+    lib.pgsr_rope_qk_bf16.restype = ctypes.c_int
+    lib.pgsr_rope_qk_bf16.argtypes = [i32, i32, i32, i32, P, P, P, ctypes.c_double, P]
     lib.pgsr_silu_mul_bf16.restype = ctypes.c_int
     lib.pgsr_silu_mul_bf16.argtypes = [i32, i32, P, P, P]
     # forget front-end (host only)

@@ -268,8 +268,9 @@ hipError_t launch_pool_init(int32_t* tables, int64_t n_table, int32_t* lens, int
                             hipStream_t s);
 hipError_t launch_rmsnorm(int32_t n, int32_t dm, const void* x, const void* g, float eps, void* y,
                           hipStream_t s);
-hipError_t launch_rope(int32_t n, int32_t heads, int32_t d, void* x, const int32_t* pos, double theta,
-                       hipStream_t s);
+// x0 [n][heads0][d] and x1 [n][heads1][d] (heads1 = 0: x0 alone)
+hipError_t launch_rope(int32_t n, int32_t heads0, int32_t heads1, int32_t d, void* x0, void* x1,
+                       const int32_t* pos, double theta, hipStream_t s);
 hipError_t launch_silu_mul(int32_t n, int32_t dff, const void* gu, void* out, hipStream_t s);
 
 // Text returned by pgsr_last_error() on this thread (host runtime).

@@ -1153,7 +1153,18 @@ int pgsr_rope_bf16(int32_t n, int32_t n_heads, int32_t head_dim, void* x, const 
   if (!(theta > 1.0) || !std::isfinite(theta)) return fail(PGSR_EINVAL, "theta must be finite and > 1");
   if (n == 0) return ok();
   if (!x || !positions) return fail(PGSR_EINVAL, "null pointer");
-  hipError_t err = launch_rope(n, n_heads, head_dim, x, positions, theta, (hipStream_t)stream);
+  hipError_t err = launch_rope(n, n_heads, 0, head_dim, x, nullptr, positions, theta, (hipStream_t)stream);
+  return err == hipSuccess ? ok() : hip_fail(err, "rope launch");
+}
+
+int pgsr_rope_qk_bf16(int32_t n, int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, void* q, void* k,
+                      const int32_t* positions, double theta, void* stream) {
+  if (n < 0 || n_q_heads <= 0 || n_kv_heads <= 0 || head_dim <= 0 || head_dim % 2)
+    return fail(PGSR_EINVAL, "n = %d, heads = %d, %d, head_dim = %d", n, n_q_heads, n_kv_heads, head_dim);
+  if (!(theta > 1.0) || !std::isfinite(theta)) return fail(PGSR_EINVAL, "theta must be finite and > 1");
+  if (n == 0) return ok();
+  if (!q || !k || !positions) return fail(PGSR_EINVAL, "null pointer");
+  hipError_t err = launch_rope(n, n_q_heads, n_kv_heads, head_dim, q, k, positions, theta, (hipStream_t)stream);
   return err == hipSuccess ? ok() : hip_fail(err, "rope launch");
 }
 

@@ -37,6 +37,13 @@ def rope_(x: torch.Tensor, positions: torch.Tensor, theta: float, stream=None) -
     return x
 
 
+def rope_qk_(q: torch.Tensor, k: torch.Tensor, positions: torch.Tensor, theta: float, stream=None) -> None:
+    """``rope_`` of q [n, n_q_heads, d] and k [n, n_kv_heads, d] in one launch."""
+    assert positions.dtype == torch.int32 and positions.is_cuda
+    N.check(N.lib.pgsr_rope_qk_bf16(q.shape[0], q.shape[1], k.shape[1], q.shape[2], q.data_ptr(), k.data_ptr(),
+                                    positions.data_ptr(), float(theta), _stream(stream)))
+
+
 def silu_mul(gate_up: torch.Tensor, out: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     n, two_ff = gate_up.shape
     out = torch.empty((n, two_ff // 2), dtype=gate_up.dtype, device=gate_up.device) if out is None else out
@@ -85,8 +92,7 @@ class DecoderReplay:
         for li, w in enumerate(self.w):
             rmsnorm(x, w["g_attn"], self.eps, out=h)
             gemm_bf16_multi(h, (w["wq"], w["wk"], w["wv"]), (q, k, v))
-            rope_(q, pos, self.theta)
-            rope_(k, pos, self.theta)
+            rope_qk_(q, k, pos, self.theta)
             rc = fn(li, [seq], [n], q, k, v, o, scale, commit=(li == last))
             if rc:
                 raise N.PgsrError(rc, N.lib.pgsr_last_error().decode())

@@ -13,6 +13,7 @@ from oracle import decoder as DEC
 from gpu_helpers import log
 
 from paper_2609_04875_amd import DecoderReplay, gemm_bf16, rmsnorm, rope_, silu_mul
+from paper_2609_04875_amd.decoder import rope_qk_
 from paper_2609_04875_amd.pool import gemm_bf16_multi, gemm_silu_bf16
 
 pytestmark = pytest.mark.gpu
@@ -48,6 +49,28 @@ def test_rope_matches_oracle_at_large_positions():
     t = _dev(x)
     rope_(t, torch.from_numpy(pos).cuda(), 5e5)
     _within_one_rounding(_f64(t), DEC.rope(x, pos, 5e5))
+
+
+@pytest.mark.parametrize("n,hq,hkv,d", [(1, 32, 8, 128), (5, 7, 1, 64), (1025, 4, 2, 128), (3, 2, 1, 256),
+                                        (6, 3, 2, 272), (9, 2, 2, 24)])
+def test_rope_of_q_and_k_in_one_call(n, hq, hkv, d):
+    """Both row kernels (one and four tokens a workgroup, a ragged last one),
+    the widest head they take, and head sizes that take the pair kernel, as does
+    a tensor off the 16-byte boundary: the same bits on every route, which
+    match the oracle."""
+    rng = np.random.default_rng(n + d)
+    q, k = bf16_round(rng.standard_normal((n, hq, d))), bf16_round(rng.standard_normal((n, hkv, d)))
+    pos = rng.integers(0, 131072, size=n).astype(np.int32)
+    pd = torch.from_numpy(pos).cuda()
+    tq, tk = _dev(q), _dev(k)
+    off = torch.empty(q.size + 2, dtype=torch.bfloat16, device="cuda")[2:].view(n, hq, d)
+    off.copy_(tq)
+    single = rope_(tq.clone(), pd, 5e5)
+    rope_qk_(tq, tk, pd, 5e5)
+    rope_(off, pd, 5e5)
+    _within_one_rounding(_f64(tq), DEC.rope(q, pos, 5e5))
+    _within_one_rounding(_f64(tk), DEC.rope(k, pos, 5e5))
+    assert torch.equal(tq, single) and torch.equal(tq, off)
 
 
 def test_silu_mul_matches_oracle():
