@@ -289,17 +289,19 @@ int pgsr_pool_set_clock_buffer(pgsr_pool *pool, void *buf, size_t bytes);
 int pgsr_pool_last_clock(pgsr_pool *pool, void *stream, double *ghz, int64_t *cycles, int64_t *ticks);
 
 /*
- * Choice of the bf16 prefill attention kernel (Algorithm 1 replay loop,
- * prefill form).  PGSR_PREFILL_AUTO (the default) runs, for a bf16 pool with
- * head_dim 128 and a GQA group dividing 32, the wide kernel (one wave per
- * SIMD, 64 query rows per wave, global->LDS tile loads) when the pool has
- * 16-token blocks, n_blocks * n_kv_heads * 4 KB <= 4 GB and no sequence of
- * the call reaches more than 130816 keys (prefix + suffix), else the
- * software-pipelined kernel (two waves per SIMD, 32 query rows per wave);
- * every other call runs the four-wave kernel.  PGSR_PREFILL_PIPELINED skips
- * the wide kernel; PGSR_PREFILL_FOUR_WAVE runs the four-wave kernel for every
- * call.  All give identical bits for every query row; the option only moves
- * time.  Host only, no device work; EINVAL for another value.
+ * Choice of the prefill attention kernel of bf16 and FP8 pools (Algorithm 1
+ * replay loop, prefill form) for head_dim 128.  PGSR_PREFILL_AUTO (the
+ * default) runs, for a bf16 pool with 16-token blocks, n_blocks * n_kv_heads *
+ * 4 KB <= 4 GB and no sequence of the call past 130816 keys (prefix + suffix),
+ * the wide kernel (one wave per SIMD, 64 query rows per wave, global->LDS tile
+ * loads) or, for calls that leave CUs idle, the narrow one (32 query rows per
+ * wave); for other bf16 pools and FP8 pools the software-pipelined kernel
+ * (32 query rows per wave, two waves per SIMD, FP8 calls that leave CUs idle
+ * one) or, for bf16 calls that leave CUs idle, the four-wave kernel.
+ * PGSR_PREFILL_PIPELINED always runs the pipelined kernel with two waves per
+ * SIMD; PGSR_PREFILL_FOUR_WAVE the four-wave kernel, as head_dim 64 does.  All
+ * give identical bits for every query row; the option only moves time.  Host
+ * only, no device work; EINVAL for another value.
  */
 enum { PGSR_PREFILL_AUTO = 0, PGSR_PREFILL_FOUR_WAVE = 1, PGSR_PREFILL_PIPELINED = 2 };
 int pgsr_pool_set_prefill_kernel(pgsr_pool *pool, int kind);

@@ -38,7 +38,7 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
 # result with VALU instructions (softmax, rescale), so its matrix results must
 # live in VGPRs: left to its heuristics the compiler
 # places them in AGPRs and copies them back on every step.
-EXTRA = {"attn_bf16_pipe.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+EXTRA = {f: ["-mllvm", "-amdgpu-mfma-vgpr-form"] for f in ("attn_bf16_pipe.hip", "attn_bf16_narrow.hip")}
 
 
 def sources():

@@ -3,9 +3,11 @@
 // rows, so every K and V^T operand read from LDS feeds two products.
 //
 // Work decomposition.  A workgroup of 4 wave64s (one per SIMD, up to 512
-// registers each) owns one KV head g and a tile of 4 * 64 / G consecutive
-// suffix tokens with the G query heads sharing g (G divides 32); wave w owns
-// two 32-row blocks of (token, head) query rows.  blockIdx.x = tile *
+// registers each) owns one KV head g and a tile of 8 * floor(32 / G) consecutive
+// suffix tokens with the G query heads sharing g; wave w owns two 32-row blocks
+// of (token, head) query rows (floor(32 / G) tokens each: where G does not divide
+// 32 the last rows are padding; 28 query / 4 KV heads, 3195 tokens against 4995:
+// 320 us, the four-wave kernel 405).  blockIdx.x = tile *
 // n_kv_heads + g keeps every tile of a KV head on one XCD; tiles are issued
 // costliest first.  The query tiling, the key tiling, the per-row arithmetic
 // and therefore every output bit are those of the two-wave pipelined kernel
@@ -96,6 +98,9 @@ __device__ __forceinline__ void static_for(F&& f, std::integer_sequence<int, I..
   (f(std::integral_constant<int, I>{}), ...);
 }
 
+// PAD: the group does not divide 32 (a separate instantiation, so that the
+// others' code stays as it is).
+template <bool PAD>
 __global__ void __launch_bounds__(kWW * 64, 1)
 attn_bf16_wide_kernel(AttnArgs a, const int32_t* __restrict__ tables, const uint16_t* __restrict__ qg_,
                       const uint16_t* __restrict__ kc, const uint16_t* __restrict__ vc,
@@ -137,7 +142,7 @@ attn_bf16_wide_kernel(AttnArgs a, const int32_t* __restrict__ tables, const uint
 #pragma unroll
   for (int b = 0; b < QB; ++b) {
     tok[b] = t0 + (w * QB + b) * TPB + r / G;
-    valid[b] = tok[b] < e.q_len;
+    valid[b] = (!PAD || r < TPB * G) && tok[b] < e.q_len;
     qpos[b] = valid[b] ? e.prefix + tok[b] : -1;
   }
   const int t_last = min(e.q_len, t0 + TW) - 1;
@@ -702,7 +707,7 @@ bool attn_bf16_wide_eligible(int head_dim, int group, int block_size, int64_t n_
                              int64_t max_kv_len) {
   // a workgroup's LDS block table holds (key tiles + 4) * 4 entries
   if ((max_kv_len + kWKT - 1) / kWKT + 4 > kWMaxIdt / 4) return false;
-  return head_dim == 128 && block_size == 16 && group >= 1 && group <= 32 && 32 % group == 0 &&
+  return head_dim == 128 && block_size == 16 && group >= 1 && group <= 32 &&
          n_blocks * n_kv_heads * 4096 <= ((int64_t)1 << 32);
 }
 
@@ -714,8 +719,12 @@ hipError_t launch_attn_bf16_wide(const AttnArgs& a, hipStream_t s) {
   if (!attn_bf16_wide_eligible(a.head_dim, group, a.block_size, a.n_blocks, a.n_kv_heads, max_kv))
     return hipErrorInvalidValue;
   const dim3 grid(a.n_tiles * a.n_kv_heads * a.n_splits), blk(kWW * 64);
-  hipLaunchKernelGGL(attn_bf16_wide_kernel, grid, blk, 0, s, a, a.tables, (const uint16_t*)a.q,
-                     (const uint16_t*)a.k_cache, (const uint16_t*)a.v_cache, (uint16_t*)a.o);
+  const auto* q = (const uint16_t*)a.q;
+  const auto* kc = (const uint16_t*)a.k_cache;
+  const auto* vc = (const uint16_t*)a.v_cache;
+  auto* o = (uint16_t*)a.o;
+  if (32 % group == 0) hipLaunchKernelGGL(attn_bf16_wide_kernel<false>, grid, blk, 0, s, a, a.tables, q, kc, vc, o);
+  else hipLaunchKernelGGL(attn_bf16_wide_kernel<true>, grid, blk, 0, s, a, a.tables, q, kc, vc, o);
   return hipGetLastError();
 }
 

@@ -239,11 +239,12 @@ bool fused_append_supported(int block_size, int head_dim);
 hipError_t launch_fused_append(const FusedAppendArgs& a, hipStream_t s);
 hipError_t launch_attn_f32(const AttnArgs& a, hipStream_t s);
 hipError_t launch_attn_bf16(const AttnArgs& a, hipStream_t s);
-// Software-pipelined bf16 prefill for head_dim 128 and GQA groups dividing
-// 32: two waves per SIMD, 32 query rows per wave, one workgroup per CU.
+// Software-pipelined prefill for head_dim 128, bf16 and FP8 pools: 32 query
+// rows per wave, one workgroup per CU of 8 waves (two per SIMD) or, for calls
+// that leave CUs idle, 4.
 bool attn_bf16_pipe_eligible(int head_dim, int group);
-int attn_bf16_pipe_tile_tokens(int group);
-hipError_t launch_attn_bf16_pipe(const AttnArgs& a, hipStream_t s);
+int attn_bf16_pipe_tile_tokens(int group, int waves);
+hipError_t launch_attn_bf16_pipe(const AttnArgs& a, int waves, bool fp8, hipStream_t s);
 // The same tiles and bits with one wave per SIMD holding 64 query rows and
 // global->LDS tile loads: 16-token blocks, pools whose layer-head block range
 // fits 32-bit byte offsets, sequences of up to 130816 keys (a workgroup's
@@ -252,6 +253,10 @@ hipError_t launch_attn_bf16_pipe(const AttnArgs& a, hipStream_t s);
 bool attn_bf16_wide_eligible(int head_dim, int group, int block_size, int64_t n_blocks, int n_kv_heads,
                              int64_t max_kv_len);
 hipError_t launch_attn_bf16_wide(const AttnArgs& a, hipStream_t s);
+// Same bits with `waves` (4 or 2) waves of 32 query rows, for calls that leave
+// most CUs idle; eligible where the wide kernel is.
+int attn_bf16_narrow_tile_tokens(int group, int waves);
+hipError_t launch_attn_bf16_narrow(const AttnArgs& a, int waves, hipStream_t s);
 // Same kernel over an FP8 E4M3 cache: codes widen to bf16 exactly on the way
 // into LDS; the K scale is in scale_log2, the V scale in o_scale.
 hipError_t launch_attn_fp8(const AttnArgs& a, hipStream_t s);

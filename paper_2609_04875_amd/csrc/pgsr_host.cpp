@@ -236,6 +236,7 @@ struct Seg {
   int32_t seq, prefix, q_len, q_off;
 };
 
+constexpr int64_t kCus = 256;
 // Split-key attention: used when a launch has fewer workgroups than this (two
 // per CU of the 256) and a workspace is available; at most kMaxSplits splits
 // (a decode step of one sequence, 8 workgroups unsplit, then fills the chip),
@@ -454,13 +455,16 @@ int do_replay(pgsr_pool* p, int32_t layer, int32_t n, const int32_t* seqs,
   for (const Seg& g : segs) decode = decode && g.q_len <= 32 / group;
   int64_t max_kv = 0;
   for (const Seg& g : segs) max_kv = std::max<int64_t>(max_kv, (int64_t)g.prefix + g.q_len);
-  const bool wide = p->dtype == PGSR_BF16 && p->prefill_kind == PGSR_PREFILL_AUTO &&
-                    attn_bf16_wide_eligible(p->d, group, p->B, p->n_blocks, p->hkv, max_kv);
-  const bool pipe = !wide && p->dtype == PGSR_BF16 &&
-                    (p->prefill_kind == PGSR_PREFILL_AUTO || p->prefill_kind == PGSR_PREFILL_PIPELINED) &&
-                    attn_bf16_pipe_eligible(p->d, group);
+  // Kernels of one arithmetic (the same bits for every row), so the choice only
+  // moves time; the tile they share decides how many splits a call takes.
+  const bool f8 = p->dtype == PGSR_FP8_E4M3;
+  const bool wide_ok = p->dtype == PGSR_BF16 && p->prefill_kind == PGSR_PREFILL_AUTO &&
+                       attn_bf16_wide_eligible(p->d, group, p->B, p->n_blocks, p->hkv, max_kv);
+  const bool pipe_ok = p->dtype != PGSR_F32 && p->prefill_kind != PGSR_PREFILL_FOUR_WAVE &&
+                       attn_bf16_pipe_eligible(p->d, group);
+  const bool split_as_wide = (wide_ok || pipe_ok) && !f8 && 32 % group == 0;
   const int tile_tokens = p->dtype == PGSR_F32 ? attn_f32_tile_tokens(p->d, group)
-                          : wide || pipe       ? attn_bf16_pipe_tile_tokens(group)
+                          : split_as_wide      ? attn_bf16_pipe_tile_tokens(group, 8)
                                                : attn_bf16_tile_tokens(p->d, group);
   for (size_t base = 0; base < segs.size(); base += kMaxSeqsPerLaunch) {
     const int32_t cnt = (int32_t)std::min<size_t>(kMaxSeqsPerLaunch, segs.size() - base);
@@ -487,16 +491,25 @@ int do_replay(pgsr_pool* p, int32_t layer, int32_t n, const int32_t* seqs,
     a.scale_log2 = (float)((double)scale * 1.4426950408889634 * (double)p->k_scale[layer]);
     a.o_scale = p->v_scale[layer];
     a.n = cnt;
-    int32_t tiles = 0;
     for (int32_t i = 0; i < cnt; ++i) {
       a.e[i].seq = chunk[i].seq;
       a.e[i].prefix = chunk[i].prefix;
       a.e[i].q_len = chunk[i].q_len;
       a.e[i].q_off = chunk[i].q_off;
-      a.e[i].tile_start = tiles;
-      tiles += cdiv(chunk[i].q_len, tile_tokens);
     }
-    a.n_tiles = tiles;
+    auto count_tiles = [&](int tokens) {
+      int64_t n_tiles = 0;
+      for (int32_t i = 0; i < cnt; ++i) n_tiles += cdiv(chunk[i].q_len, tokens);
+      return n_tiles;
+    };
+    auto set_tiles = [&](int tokens) {
+      a.n_tiles = 0;
+      for (int32_t i = 0; i < cnt; ++i) {
+        a.e[i].tile_start = a.n_tiles;
+        a.n_tiles += cdiv(chunk[i].q_len, tokens);
+      }
+    };
+    set_tiles(tile_tokens);
     a.n_splits = 1;
     a.split_len = 0;
     a.n_rows = off * p->hq;                        // packed query rows of the whole call
@@ -530,8 +543,8 @@ int do_replay(pgsr_pool* p, int32_t layer, int32_t n, const int32_t* seqs,
     // a workspace for the partials: splits at absolute multiples of split_len.
     // (the bf16 kernel packs a KV head's query heads into one workgroup, the
     // fp32 kernel takes one query head per workgroup)
-    const int64_t wgs = (int64_t)tiles * (p->dtype == PGSR_F32 ? p->hq : p->hkv);
-    const int64_t target = wide || pipe ? kSplitTargetWorkgroupsPipe : kSplitTargetWorkgroups;
+    const int64_t wgs = (int64_t)a.n_tiles * (p->dtype == PGSR_F32 ? p->hq : p->hkv);
+    const int64_t target = split_as_wide ? kSplitTargetWorkgroupsPipe : kSplitTargetWorkgroups;
     if (ws_bytes > 0 && wgs < target) {
       int32_t max_key = 0;
       for (int32_t i = 0; i < cnt; ++i) max_key = std::max(max_key, chunk[i].prefix + chunk[i].q_len);
@@ -546,18 +559,42 @@ int do_replay(pgsr_pool* p, int32_t layer, int32_t n, const int32_t* seqs,
         a.ws_ml = a.ws_acc + (int64_t)a.n_splits * a.n_rows * p->d;
       }
     }
-    if (p->timing && p->clk && (wide || pipe)) {
+    // Launches that leave CUs idle are as long as one workgroup's walk over its
+    // keys, so the kernel with the shortest step is taken as long as every
+    // workgroup has a CU (us per call, 32 query / 8 KV heads, 8189 cached keys,
+    // 16-token blocks): bf16, 102 tokens: narrow (two waves) 139, narrow (four)
+    // 140, four-wave 181, wide 185; 1024 tokens (256 workgroups of four waves):
+    // narrow 170, four-wave 205, wide 211; 1500 tokens: narrow 300, wide 233.
+    // FP8, 1024 tokens: pipelined with four waves 178, four-wave 209, pipelined
+    // with eight 236; 2048 tokens: 346, 316 and 297.  Pools that the wide kernel
+    // does not take (32- and 64-token blocks): four-wave, then pipelined.
+    auto fits = [&](int tokens) { return count_tiles(tokens) * p->hkv * a.n_splits <= kCus; };
+    int narrow = 0, pipe = 0;       // waves per workgroup of the kernel taken
+    bool wide = false;
+    if (wide_ok) {
+      narrow = fits(attn_bf16_narrow_tile_tokens(group, 2))   ? 2
+               : fits(attn_bf16_narrow_tile_tokens(group, 4)) ? 4
+                                                              : 0;
+      wide = narrow == 0;
+      set_tiles(wide ? attn_bf16_pipe_tile_tokens(group, 8) : attn_bf16_narrow_tile_tokens(group, narrow));
+    } else if (pipe_ok) {
+      const bool few = p->prefill_kind == PGSR_PREFILL_AUTO && fits(attn_bf16_pipe_tile_tokens(group, 4));
+      pipe = !few ? 8 : f8 ? 4 : 0;
+      set_tiles(pipe ? attn_bf16_pipe_tile_tokens(group, pipe) : attn_bf16_tile_tokens(p->d, group));
+    }
+    if (p->timing && p->clk && (narrow || wide || pipe)) {
       hipError_t err = hipMemsetAsync(p->clk, 0, (size_t)p->clk_n * 4 * sizeof(uint64_t), st);
       if (err != hipSuccess) return hip_fail(err, "clock probe reset");
       a.clk = p->clk;
       a.clk_n = p->clk_n;
       p->clk_written = true;
     }
-    hipError_t err = p->dtype == PGSR_F32    ? launch_attn_f32(a, st)
-                     : wide                  ? launch_attn_bf16_wide(a, st)
-                     : pipe                  ? launch_attn_bf16_pipe(a, st)
-                     : p->dtype == PGSR_BF16 ? launch_attn_bf16(a, st)
-                                             : launch_attn_fp8(a, st);
+    hipError_t err = p->dtype == PGSR_F32 ? launch_attn_f32(a, st)
+                     : narrow             ? launch_attn_bf16_narrow(a, narrow, st)
+                     : wide               ? launch_attn_bf16_wide(a, st)
+                     : pipe               ? launch_attn_bf16_pipe(a, pipe, f8, st)
+                     : f8                 ? launch_attn_fp8(a, st)
+                                          : launch_attn_bf16(a, st);
     if (err == hipSuccess && a.n_splits > 1) err = launch_split_combine(a, p->dtype == PGSR_F32, st);
     if (err != hipSuccess) return hip_fail(err, "attention launch");
   }

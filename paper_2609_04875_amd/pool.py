@@ -124,8 +124,8 @@ class KVPool:
         N.check(N.lib.pgsr_pool_set_kv_scales(self._h, ks, vs))
 
     def set_prefill_kernel(self, kind: str) -> None:
-        """bf16 prefill kernel: "auto" (wide, else pipelined, where they apply),
-        "pipelined" (never the wide kernel) or "four_wave"."""
+        """Prefill kernel of a head_dim 128 bf16 or FP8 pool: "auto" (by size,
+        cache and block size), "pipelined" or "four_wave"; the same bits."""
         code = {"auto": 0, "four_wave": 1, "pipelined": 2}[kind]
         N.check(N.lib.pgsr_pool_set_prefill_kernel(self._h, code))
 

@@ -270,3 +270,33 @@ def test_fp8_fork_copies_codes():
             wk, wv = _oracle_codes(opool, layer, s, L)
             _assert_codes_equal(gk, wk, f"seq {s} layer {layer} K")
             _assert_codes_equal(gv, wv, f"seq {s} layer {layer} V")
+
+
+@pytest.mark.parametrize("hq,hkv,B,ps", [
+    (32, 8, 16, [(200, 1024)]), (32, 8, 16, [(200, 1025)]),     # 256 workgroups of 4 waves, and one row more
+    (32, 8, 32, [(129, 300), (5, 40)]), (32, 8, 64, [(64, 1100)]),
+    (28, 4, 16, [(300, 77)]), (28, 4, 32, [(50, 1100)])])       # G = 7: padded rows
+def test_fp8_default_prefill_kernel_equals_four_wave(hq, hkv, B, ps):
+    """The pipelined kernel with 4 and with 8 waves and the four-wave kernel
+    take every row through the same operations on the widened codes."""
+    geom = W.AttnGeometry(hq, hkv, 128)
+    log(f"fp8 prefill kernels {hq}/{hkv} B={B} {ps}")
+    rng = np.random.default_rng(hq + B)
+    eps = [W.draw_episode(rng, geom, "bf16", P, S, P + S + 3) for P, S in ps]
+    outs = []
+    for kind in ("auto", "pipelined", "four_wave"):
+        nb = sum(-(-(P + S + 3) // B) for P, S in ps)
+        pool = _pool(geom, 1, 2 * nb + 4, len(ps), nb + 2, B)
+        pool.set_kv_scales([5 / 448], [4 / 448])
+        pool.set_prefill_kernel(kind)
+        for i, e in enumerate(eps):
+            cq, ck, cv = (dev(e.contaminated(x), "bf16") for x in ("q", "k", "v"))
+            assert pool.replay(0, [i], [e.t_contaminated], cq, ck, cv, torch.empty_like(cq), 128 ** -0.5) == 0
+            assert pool.crop([i], [e.prefix], poison=True) == 0
+        q, k, v = (torch.cat([dev(getattr(e, x)[e.prefix:], "bf16") for e in eps]) for x in ("q", "k", "v"))
+        o = torch.empty_like(q)
+        assert pool.replay(0, list(range(len(ps))), [S for _, S in ps], q, k, v, o, 128 ** -0.5) == 0
+        torch.cuda.synchronize()
+        assert torch.isfinite(o.float()).all()
+        outs.append(o)
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])

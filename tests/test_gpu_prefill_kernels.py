@@ -168,3 +168,58 @@ def test_longest_sequences_for_the_lds_block_table(P, S):
     ref = oracle_suffix(eps[0], scale, rows=rows)
     got = auto.reshape(-1, 128)[torch.from_numpy(rows).cuda()].float().cpu().numpy()
     assert_close(got, ref, "bf16", f"P={P} S={S}")
+
+
+# What decides the default kernel is the number of workgroups of narrow tiles (2, then 4 waves of
+# floor(32 / G) tokens, at most 256 workgroups), so: one case just inside and one just past each line, a
+# ragged batch of short sequences past it, groups that do not divide 32 (padded rows), splits, both
+# block-size families
+@pytest.mark.parametrize("hq,hkv,B,ps,ws_tokens", [
+    (32, 8, 16, [(45, 512)], 0),                       # 32 tiles of 2 waves x 8 heads = 256
+    (32, 8, 16, [(45, 513)], 0),                       # 33: four waves
+    (32, 8, 16, [(200, 1024)], 0),                     # 32 tiles of 4 waves x 8 heads = 256
+    (32, 8, 16, [(200, 1025)], 0),                     # 33: wide
+    (64, 2, 16, [(33, 601)], 0),                       # G = 32, wide
+    (16, 16, 16, [(7, 1900), (70, 150)], 0),           # G = 1, wide
+    (32, 8, 16, [(37 * i, 33 - i % 5) for i in range(40)], 0),
+    (28, 4, 16, [(300, 77)], 0),                       # G = 7: two waves
+    (28, 4, 16, [(100, 700), (3, 20)], 0),             # four waves
+    (28, 4, 16, [(500, 1100)], 0),                     # wide
+    (20, 4, 16, [(129, 50)], 0),                       # G = 5
+    (28, 4, 32, [(129, 900)], 0),                      # pipelined with padded rows
+    (28, 4, 64, [(64, 40)], 0),                        # four-wave
+    (32, 8, 16, [(900, 40)], 40),                      # split keys
+    (28, 4, 16, [(2000, 130)], 130),
+])
+def test_default_kernel_equals_four_wave_at_its_lines(hq, hkv, B, ps, ws_tokens):
+    geom = W.AttnGeometry(hq, hkv, 128)
+    log(f"default kernel at its lines {hq}/{hkv} B={B} {len(ps)} episodes {ps[:3]} workspace {ws_tokens}")
+    rng = np.random.default_rng(hq + B + sum(p + 3 * s for p, s in ps))
+    eps = [W.draw_episode(rng, geom, "bf16", P, S, P + S + 3) for P, S in ps]
+    scale = 128 ** -0.5
+    outs = {}
+    for kind in ("auto", "pipelined", "four_wave"):
+        nb = sum(_blocks(e.t_contaminated, B) + _blocks(e.t_sanitized, B) for e in eps) + 4
+        mbps = max(_blocks(max(e.t_contaminated, e.t_sanitized), B) for e in eps) + 2
+        pool = make_pool(geom, "bf16", nb, len(eps), mbps, block_size=B, split_q=ws_tokens, max_splits=8)
+        if not ws_tokens:                # a split call's bits depend on its number of splits
+            pool.set_prefill_kernel(kind)
+        elif kind != "auto":
+            continue
+        for i, e in enumerate(eps):
+            contaminated_then_crop(pool, e, i, scale, poison=True)
+        q, k, v = (torch.cat([dev(getattr(e, x)[e.prefix:], "bf16") for e in eps]) for x in ("q", "k", "v"))
+        o = torch.empty_like(q)
+        assert pool.replay(0, list(range(len(eps))), [e.suffix for e in eps], q, k, v, o, scale) == 0
+        torch.cuda.synchronize()
+        outs[kind] = o
+    for kind, o in outs.items():
+        assert torch.equal(o, outs["auto"]), f"{kind} differs from the default kernel"
+    off = 0
+    for i, e in enumerate(eps):
+        if i < 2:
+            rows = np.unique(np.concatenate([np.arange(0, e.suffix * hq, 37), np.arange(e.suffix * hq - hq, e.suffix * hq)]))
+            got = outs["auto"][off:off + e.suffix].reshape(-1, 128)[torch.from_numpy(rows).cuda()]
+            assert_close(got.float().cpu().numpy(), oracle_suffix(e, scale, rows=rows), "bf16",
+                         f"P={e.prefix} S={e.suffix}")
+        off += e.suffix
