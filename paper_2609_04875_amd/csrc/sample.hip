@@ -27,6 +27,17 @@ struct Philox4 {
   uint64_t w[4];
 };
 
+// 64 x 64 -> 128-bit product from four 32-bit multiply-adds (the low and the
+// high half asked for separately cost two multiplies more).
+__device__ inline void mul128(uint64_t a, uint64_t b, uint64_t& hi, uint64_t& lo) {
+  const uint32_t al = (uint32_t)a, ah = (uint32_t)(a >> 32), bl = (uint32_t)b, bh = (uint32_t)(b >> 32);
+  const uint64_t p0 = (uint64_t)al * bl;
+  const uint64_t p1 = (uint64_t)ah * bl + (p0 >> 32);
+  const uint64_t p2 = (uint64_t)al * bh + (uint32_t)p1;
+  hi = (uint64_t)ah * bh + (p1 >> 32) + (p2 >> 32);
+  lo = (p2 << 32) | (uint32_t)p0;
+}
+
 // Ten Philox4x64 rounds on counter c with key k.
 __device__ inline Philox4 philox4x64_10(uint64_t c0, uint64_t c1, uint64_t c2, uint64_t c3, uint64_t k0,
                                         uint64_t k1) {
@@ -34,8 +45,9 @@ __device__ inline Philox4 philox4x64_10(uint64_t c0, uint64_t c1, uint64_t c2, u
   constexpr uint64_t W0 = 0x9E3779B97F4A7C15ull, W1 = 0xBB67AE8584CAA73Bull;
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
-    const uint64_t lo0 = M0 * c0, hi0 = __umul64hi(M0, c0);
-    const uint64_t lo1 = M1 * c2, hi1 = __umul64hi(M1, c2);
+    uint64_t lo0, hi0, lo1, hi1;
+    mul128(M0, c0, hi0, lo0);
+    mul128(M1, c2, hi1, lo1);
     const uint64_t n0 = hi1 ^ c1 ^ k0, n2 = hi0 ^ c3 ^ k1;
     c0 = n0;
     c1 = lo1;
@@ -45,6 +57,29 @@ __device__ inline Philox4 philox4x64_10(uint64_t c0, uint64_t c1, uint64_t c2, u
     k1 += W1;
   }
   return Philox4{{c0, c1, c2, c3}};
+}
+
+// Philox word -> the 23 bits that make u = (k + 1/2) / 2^23
+__device__ inline uint32_t noise_bits(uint64_t w) { return (uint32_t)(w >> 41); }
+
+// The score that decides: l / T - log(-log u) in fp32.
+__device__ inline float exact_score(float l, float temperature, uint32_t k) {
+  const float u = ((float)k + 0.5f) * (1.f / 8388608.f);
+  return l / temperature - logf(-logf(u));
+}
+
+// The same to about 1e-5 (plus 2^-22 of |l / T|), in a fifth of the
+// instructions: two hardware logarithms, a multiply for the division.  Near
+// u = 1 the series of -ln(1 - t) replaces the first logarithm (t = 1 - u is
+// exact; the tail left out is below 2e-5 of it).  NaN counts as -inf.
+__device__ inline float rough_score(float l, float inv_temperature, uint32_t k) {
+  constexpr float kLn2 = 0.69314718056f;
+  const float kf = (float)k;
+  const float t = (8388607.5f - kf) * (1.f / 8388608.f);
+  const float near1 = t * fmaf(t, fmaf(t, fmaf(t, 0.25f, 1.f / 3.f), 0.5f), 1.f);
+  const float away = -kLn2 * __builtin_amdgcn_logf((kf + 0.5f) * (1.f / 8388608.f));
+  const float w = t < 0.1f ? near1 : away;
+  return fmaxf(fmaf(l, inv_temperature, -kLn2 * __builtin_amdgcn_logf(w)), -INFINITY);
 }
 
 __device__ inline float load_logit(const float* p, int64_t i) { return p[i]; }
@@ -70,20 +105,36 @@ __device__ inline uint64_t max_key_wave(uint64_t k) {
   return k;
 }
 
+// Four consecutive logits from v0 (a multiple of 4); entries at or past v_hi
+// read as -inf.  VEC: rows start on the boundary of one wide load.
+template <typename T, bool VEC>
+__device__ inline void load4(const T* lr, int32_t v0, int32_t v_hi, float (&l)[4]) {
+  if constexpr (VEC) {                              // vocab, so v_hi, is a multiple of 4
+    if constexpr (sizeof(T) == 2) {
+      const uint2 w = *(const uint2*)(lr + v0);
+      l[0] = __uint_as_float(w.x << 16);
+      l[1] = __uint_as_float(w.x & 0xFFFF0000u);
+      l[2] = __uint_as_float(w.y << 16);
+      l[3] = __uint_as_float(w.y & 0xFFFF0000u);
+    } else {
+      const float4 w = *(const float4*)(lr + v0);
+      l[0] = w.x;
+      l[1] = w.y;
+      l[2] = w.z;
+      l[3] = w.w;
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) l[j] = v0 + j < v_hi ? load_logit(lr, v0 + j) : -INFINITY;
+  }
+}
+
+// Best key over this thread's entries, every entry scored exactly.
 template <typename T>
-__global__ void __launch_bounds__(kThreads) sample_chunk_kernel(SampleArgs a, const T* __restrict__ logits,
-                                                                int32_t* __restrict__ tokens) {
-  __shared__ uint64_t red[kThreads / 64];
-  const int row = blockIdx.x / a.n_chunks, chunk = blockIdx.x % a.n_chunks;
-  const int64_t grow = (int64_t)a.row0 + row;
-  const T* lr = logits + grow * a.vocab;
-  const int32_t v_lo = chunk * a.chunk_len;
-  const int32_t v_hi = min(a.vocab, v_lo + a.chunk_len);
+__device__ inline uint64_t scan_exact(const T* lr, const SampleArgs& a, uint64_t pos, uint64_t str, int32_t v_lo,
+                                      int32_t v_hi) {
   const bool hot = a.temperature > 0.f;
-  const uint64_t pos = (uint64_t)a.position[row], str = (uint64_t)a.stream[row];
   uint64_t best = 0;
-  // Philox blocks of 4 entries; chunk_len is a multiple of 4, so blocks never
-  // straddle two chunks.
   for (int32_t v0 = v_lo + 4 * (int32_t)threadIdx.x; v0 < v_hi; v0 += 4 * kThreads) {
     Philox4 r{};
     if (hot) r = philox4x64_10((uint64_t)(v0 / 4), pos, str, 0, a.seed, 0);
@@ -92,13 +143,72 @@ __global__ void __launch_bounds__(kThreads) sample_chunk_kernel(SampleArgs a, co
       const int32_t v = v0 + j;
       if (v >= v_hi) break;
       float score = load_logit(lr, v);
-      if (hot) {
-        const float u = ((float)(uint32_t)(r.w[j] >> 41) + 0.5f) * (1.f / 8388608.f);
-        score = score / a.temperature - logf(-logf(u));
-      }
+      if (hot) score = exact_score(score, a.temperature, noise_bits(r.w[j]));
       const uint64_t k = make_key(score, v);
       best = k > best ? k : best;
     }
+  }
+  return best;
+}
+
+// Bound by ALU: ten Philox rounds of two 64 x 64-bit products per four
+// entries, then the scores.  Scoring every entry exactly (two logf, a division)
+// costs as much as the generator, and only the winner's score has to be exact:
+// each thread keeps its best rough score with what made it (and its second
+// best), the workgroup takes the best rough score of the chunk, and the threads
+// within twice the rough score's error of it score their candidate exactly.  A
+// thread whose second best is within it too (or a row of infinities, where no
+// margin holds) scans its entries again exactly.  32 rows x 128256 bf16 logits:
+// 21-22 -> 14.5 us with the reduction, where the calling program's own time per
+// call is as long; 64 x 151936: 39.5 -> 28.5 us.
+template <typename T, bool VEC>
+__global__ void __launch_bounds__(kThreads) sample_chunk_kernel(SampleArgs a, const T* __restrict__ logits,
+                                                                int32_t* __restrict__ tokens) {
+  __shared__ uint64_t red[kThreads / 64];
+  __shared__ float redf[kThreads / 64];
+  const int row = blockIdx.x / a.n_chunks, chunk = blockIdx.x % a.n_chunks;
+  const int64_t grow = (int64_t)a.row0 + row;
+  const T* lr = logits + grow * a.vocab;
+  const int32_t v_lo = chunk * a.chunk_len;
+  const int32_t v_hi = min(a.vocab, v_lo + a.chunk_len);
+  const uint64_t pos = (uint64_t)a.position[row], str = (uint64_t)a.stream[row];
+  uint64_t best = 0;
+  // Philox blocks of 4 entries; chunk_len is a multiple of 4, so blocks never
+  // straddle two chunks.
+  if (a.temperature > 0.f) {
+    const float inv_t = 1.f / a.temperature;
+    float top = -INFINITY, second = -INFINITY, top_l = 0.f;
+    uint32_t top_k = 0;
+    int32_t top_v = 0;
+    for (int32_t v0 = v_lo + 4 * (int32_t)threadIdx.x; v0 < v_hi; v0 += 4 * kThreads) {
+      float l[4];
+      load4<T, VEC>(lr, v0, v_hi, l);
+      const Philox4 r = philox4x64_10((uint64_t)(v0 / 4), pos, str, 0, a.seed, 0);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const uint32_t k = noise_bits(r.w[j]);
+        const float s = rough_score(l[j], inv_t, k);
+        second = __builtin_amdgcn_fmed3f(s, top, second);   // second <= top: the middle one of the three
+        const bool better = s > top;
+        top = better ? s : top;
+        top_l = better ? l[j] : top_l;
+        top_k = better ? k : top_k;
+        top_v = better ? v0 + j : top_v;
+      }
+    }
+    float m = top;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
+    if ((threadIdx.x & 63) == 0) redf[threadIdx.x >> 6] = m;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kThreads / 64; ++w) m = fmaxf(m, redf[w]);
+    // NaN where the best is infinite: then no thread is below the line
+    const float line = m - (2e-3f + 2e-6f * fabsf(m));
+    if (!(second < line)) best = scan_exact(lr, a, pos, str, v_lo, v_hi);
+    else if (!(top < line)) best = make_key(exact_score(top_l, a.temperature, top_k), top_v);
+  } else {
+    best = scan_exact(lr, a, pos, str, v_lo, v_hi);
   }
   best = max_key_wave(best);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = best;
@@ -134,12 +244,17 @@ hipError_t launch_sample(const SampleArgs& a, int dtype, const void* logits, int
                          hipStream_t s) {
   if (a.n <= 0) return hipSuccess;
   dim3 grid(a.n * a.n_chunks);
-  if (dtype == 1)
-    hipLaunchKernelGGL(sample_chunk_kernel<uint16_t>, grid, dim3(kThreads), 0, s, a,
-                       (const uint16_t*)logits, tokens);
+  // four logits per load where every row starts on its boundary
+  const size_t eb = dtype == 1 ? 2 : 4;
+  const bool vec = a.vocab % 4 == 0 && ((uintptr_t)logits & (4 * eb - 1)) == 0;
+  if (dtype == 1 && vec)
+    hipLaunchKernelGGL((sample_chunk_kernel<uint16_t, true>), grid, dim3(kThreads), 0, s, a, (const uint16_t*)logits, tokens);
+  else if (dtype == 1)
+    hipLaunchKernelGGL((sample_chunk_kernel<uint16_t, false>), grid, dim3(kThreads), 0, s, a, (const uint16_t*)logits, tokens);
+  else if (vec)
+    hipLaunchKernelGGL((sample_chunk_kernel<float, true>), grid, dim3(kThreads), 0, s, a, (const float*)logits, tokens);
   else
-    hipLaunchKernelGGL(sample_chunk_kernel<float>, grid, dim3(kThreads), 0, s, a, (const float*)logits,
-                       tokens);
+    hipLaunchKernelGGL((sample_chunk_kernel<float, false>), grid, dim3(kThreads), 0, s, a, (const float*)logits, tokens);
   return hipGetLastError();
 }
 

@@ -82,3 +82,42 @@ def test_frequencies_follow_softmax():
     p = np.exp(np.array([0.5, -1.0, 2.0, 0.0, 1.0]) / T)
     p /= p.sum()
     assert np.abs(freq - p).max() < 0.03
+
+
+@pytest.mark.parametrize("vocab,dtype", [(1024, torch.bfloat16), (1021, torch.float32), (20000, torch.float32),
+                                         (128256, torch.bfloat16), (3, torch.bfloat16)])
+@pytest.mark.parametrize("shape", ["flat", "peaked", "few", "huge"])
+def test_rough_scores_never_decide(vocab, dtype, shape):
+    """Rows on which the candidates' rough scores lie close together or on
+    which the margin is large: equal logits (the noise alone decides), twenty
+    likely entries, a row of few distinct values, logits of a million."""
+    log(f"sampling {shape} vocab={vocab} {dtype}")
+    rng = np.random.default_rng(vocab + len(shape))
+    n = 5
+    x = {"flat": np.zeros((n, vocab)), "peaked": rng.standard_normal((n, vocab)),
+         "few": rng.integers(-2, 3, size=(n, vocab)) * 0.5, "huge": rng.standard_normal((n, vocab)) * 1e6}[shape]
+    if shape == "peaked":
+        x[:, rng.integers(vocab, size=20)] += 14
+    t = torch.from_numpy(x.astype(np.float32)).cuda().to(dtype)
+    streams, positions = list(range(n)), [11 * i for i in range(n)]
+    ws = torch.empty(max(sample_workspace_bytes(n, vocab), 1), dtype=torch.uint8, device="cuda")
+    for T in (0.7, 1.3):
+        for w in (None, ws):
+            got = sample_tokens(t, T, 77, streams, positions, workspace=w).cpu().numpy()
+            _check(got, t.float().cpu().numpy().astype(np.float64), T, 77, streams, positions)
+
+
+def test_infinities_and_nan_with_noise():
+    inf, nan = float("inf"), float("nan")
+    x = torch.zeros(6, 1500, device="cuda")
+    x[0] = -inf
+    x[0, 1300] = -5.0                       # the one finite entry
+    x[1] = -inf                             # all equal: the lowest index
+    x[2] = nan
+    x[3, 700] = x[3, 1400] = inf
+    x[4] = nan
+    x[4, 9] = 0.0
+    x[5, 3:] = -inf
+    for logits in (x, x[:, :1499].contiguous(), x.to(torch.bfloat16)):
+        got = sample_tokens(logits, 0.7, 1, list(range(6)), [0] * 6).cpu().tolist()
+        assert got[:5] == [1300, 0, 0, 700, 9] and got[5] < 3
