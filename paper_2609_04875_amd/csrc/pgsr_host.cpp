@@ -242,6 +242,9 @@ constexpr int64_t kCus = 256;
 // (a decode step of one sequence, 8 workgroups unsplit, then fills the chip),
 // split boundaries at multiples of the 64-key tile.
 constexpr int64_t kSplitTargetWorkgroups = 512;
+// fp32 calls are cut into splits as if a workgroup took this many tokens (it
+// takes 32): more, shorter key ranges round less.
+constexpr int32_t kF32SplitTokens = 64;
 // The pipelined bf16 kernel holds a CU alone (one wave per SIMD).
 constexpr int64_t kSplitTargetWorkgroupsPipe = 256;
 constexpr int64_t kMaxSplits = 32;
@@ -463,7 +466,7 @@ int do_replay(pgsr_pool* p, int32_t layer, int32_t n, const int32_t* seqs,
   const bool pipe_ok = p->dtype != PGSR_F32 && p->prefill_kind != PGSR_PREFILL_FOUR_WAVE &&
                        attn_bf16_pipe_eligible(p->d, group);
   const bool split_as_wide = (wide_ok || pipe_ok) && !f8 && 32 % group == 0;
-  const int tile_tokens = p->dtype == PGSR_F32 ? attn_f32_tile_tokens(p->d, group)
+  const int tile_tokens = p->dtype == PGSR_F32 ? kF32SplitTokens
                           : split_as_wide      ? attn_bf16_pipe_tile_tokens(group, 8)
                                                : attn_bf16_tile_tokens(p->d, group);
   for (size_t base = 0; base < segs.size(); base += kMaxSeqsPerLaunch) {
@@ -571,7 +574,9 @@ int do_replay(pgsr_pool* p, int32_t layer, int32_t n, const int32_t* seqs,
     auto fits = [&](int tokens) { return count_tiles(tokens) * p->hkv * a.n_splits <= kCus; };
     int narrow = 0, pipe = 0;       // waves per workgroup of the kernel taken
     bool wide = false;
-    if (wide_ok) {
+    if (p->dtype == PGSR_F32) {
+      set_tiles(attn_f32_tile_tokens(p->d, group));
+    } else if (wide_ok) {
       narrow = fits(attn_bf16_narrow_tile_tokens(group, 2))   ? 2
                : fits(attn_bf16_narrow_tile_tokens(group, 4)) ? 4
                                                               : 0;

@@ -322,3 +322,27 @@ def test_long_horizon_chunked_full_size_sampled():
     rows = _sample_rows(rng, ep.suffix, 32, 48)
     ref = oracle_suffix(ep, w.scale, rows=rows)
     assert_close(o.float().cpu().numpy().reshape(-1, 128)[rows], ref, "bf16", w.name)
+
+
+@pytest.mark.parametrize("hq,hkv,d,B,P,S", [
+    (4, 2, 64, 16, 35, 17), (8, 8, 128, 32, 129, 33),       # ragged last key tile and row block
+    (2, 1, 64, 64, 63, 65), (6, 2, 128, 16, 0, 31),         # one tile over a block, no prefix
+    (8, 8, 64, 16, 48, 32), (2, 2, 128, 64, 5, 1),          # whole tiles; fewer tiles than waves
+])
+def test_fp32_tiles_and_reset(hq, hkv, d, B, P, S):
+    """fp32 over poisoned released slots at the edges of 16-key tiles, 16-row
+    blocks and cache blocks, against the oracle; the full reset agrees bitwise."""
+    geom = W.AttnGeometry(hq, hkv, d)
+    log(f"fp32 {hq}/{hkv} d={d} B={B} P={P} S={S}")
+    ep = W.draw_episode(np.random.default_rng(hq * d + P + S), geom, "f32", P, S, P + S + 5)
+    scale = d ** -0.5
+    nb = -(-(P + S + 5) // B)
+    pool = make_pool(geom, "f32", 2 * nb + 4, 2, nb + 2, block_size=B)
+    contaminated_then_crop(pool, ep, 0, scale, poison=True)
+    o = _replay(pool, ep, 0, scale)
+    assert_close(o.cpu().numpy(), oracle_suffix(ep, scale), "f32", "fp32 edges")
+    fq, fk, fv = (dev(getattr(ep, x), "f32") for x in ("q", "k", "v"))
+    fo = torch.empty_like(fq)
+    assert pool.full_reset(0, [1], [P + S], fq, fk, fv, fo, scale) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(fo[P:], o)
