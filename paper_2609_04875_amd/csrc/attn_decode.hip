@@ -70,12 +70,16 @@ attn_decode_kernel(AttnArgs a, const int32_t* __restrict__ tables, const uint16_
 
   const int lane = threadIdx.x & 63, r = lane & 31, hh = lane >> 5;
   const int hkv = a.n_kv_heads;
-  const int64_t wid = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (wid >= (int64_t)a.n * hkv * a.n_splits) return;
-  const int split = (int)(wid % a.n_splits);
-  const int unit = (int)(wid / a.n_splits);
-  const int g = unit % hkv;
-  const AttnEntry e = a.e[unit / hkv];
+  const int wid = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (wid >= a.n_tiles) return;
+  // Waves are numbered through the entries (tile_start: an entry's first), each
+  // with its own number of splits: lane i looks at entry i.
+  static_assert(kMaxSeqsPerLaunch <= 64, "one entry per lane");
+  const int ei = __popcll(__ballot(lane < a.n && a.e[min(lane, a.n - 1)].tile_start <= wid)) - 1;
+  const AttnEntry e = a.e[ei];
+  const int ns = a.n_splits > 1 ? (e.prefix + e.q_len - 1) / a.split_len + 1 : 1;
+  const int split = (wid - e.tile_start) % ns;
+  const int g = (wid - e.tile_start) / ns;
   const int G = a.n_q_heads / hkv;
   const int TPW = 32 / G;
   const int tok = r / G, hq = g * G + r % G;
@@ -86,7 +90,6 @@ attn_decode_kernel(AttnArgs a, const int32_t* __restrict__ tables, const uint16_
   // tile, so tiles never cross a split boundary (only kv_len is unaligned).
   const int key_lo = a.n_splits > 1 ? split * a.split_len : 0;
   const int key_hi = a.n_splits > 1 ? min(kv_len, key_lo + a.split_len) : kv_len;
-  if (key_lo >= key_hi) return;
 
   // Q^T operand: lane (row r, half hh) holds d in [hh D/2 + 8 ds, +8).
   bf16x8 qb[kQLds ? 1 : NDS];
@@ -267,8 +270,7 @@ attn_decode_kernel(AttnArgs a, const int32_t* __restrict__ tables, const uint16_
 template <int D, int B, bool F8>
 void launch_dec(const AttnArgs& a, hipStream_t s) {
   using CT = std::conditional_t<F8, uint8_t, uint16_t>;
-  const int64_t waves = (int64_t)a.n * a.n_kv_heads * a.n_splits;
-  hipLaunchKernelGGL((attn_decode_kernel<D, B, F8>), dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s, a,
+  hipLaunchKernelGGL((attn_decode_kernel<D, B, F8>), dim3((unsigned)((a.n_tiles + 3) / 4)), dim3(256), 0, s, a,
                      a.tables, (const uint16_t*)a.q, (const CT*)a.k_cache, (const CT*)a.v_cache,
                      (uint16_t*)a.o);
 }

@@ -170,7 +170,7 @@ struct AttnEntry {
   int32_t prefix;      // P: queries sit at absolute positions P .. P+S-1
   int32_t q_len;       // S
   int32_t q_off;       // first row of this sequence in q / o
-  int32_t tile_start;  // prefix sum of query tiles over entries
+  int32_t tile_start;  // prefix sum of query tiles (decode: of waves) over entries
 };
 
 struct AttnArgs {

@@ -250,13 +250,21 @@ constexpr int64_t kSplitTargetWorkgroupsPipe = 256;
 constexpr int64_t kMaxSplits = 32;
 constexpr int32_t kSplitAlign = 64;
 // Decode kernel (calls whose sequences all fit one wave's 32 query rows, with
-// a workspace): aim for eight waves per CU, at most 64 splits of at least 256
-// keys each.
+// a workspace): the shortest split, of at least 64 keys and at most 64 to a
+// sequence, whose waves over all sequences fit the eight that a CU holds at
+// once.  Counting each sequence's own splits fills the chip for ragged lengths
+// too (32 sequences of 1024 to 16384 keys: 124 us against 142 with an FP8 cache
+// and 215 against 267 in bf16, where one count for all, from the number of
+// sequences, left half of the waves without keys; 48 x 4000 FP8, where it left
+// a second round: 96 against 119).  A larger target makes a second round (3072 waves: 32 x
+// 8192 bf16 217 against 190 us).  Few sequences are a serial walk per wave, one
+// tile's latency (about 1.5 us) after the other: two tiles instead of eight
+// take 16 against 20 us a call at 1331 keys; 128 keys 19.
 #ifndef PGSR_DECODE_TARGET_WAVES
 #define PGSR_DECODE_TARGET_WAVES 2048
 #endif
 #ifndef PGSR_DECODE_MIN_SPLIT_KEYS
-#define PGSR_DECODE_MIN_SPLIT_KEYS 256
+#define PGSR_DECODE_MIN_SPLIT_KEYS 64
 #endif
 constexpr int64_t kDecodeTargetWaves = PGSR_DECODE_TARGET_WAVES;
 constexpr int64_t kDecodeMaxSplits = 64;
@@ -523,19 +531,33 @@ int do_replay(pgsr_pool* p, int32_t layer, int32_t n, const int32_t* seqs,
     if (decode) {
       int32_t max_key = 0;
       for (int32_t i = 0; i < cnt; ++i) max_key = std::max(max_key, chunk[i].prefix + chunk[i].q_len);
-      const int64_t units = (int64_t)cnt * p->hkv;
+      auto waves = [&](int64_t len) {
+        int64_t w = 0;
+        for (int32_t i = 0; i < cnt; ++i) w += cdiv((int64_t)chunk[i].prefix + chunk[i].q_len, len);
+        return w * p->hkv;
+      };
+      const int64_t kt = attn_decode_keys_per_tile();
       const int64_t per_split = (int64_t)a.n_rows * ((int64_t)p->d + 2) * (int64_t)sizeof(float);
-      int64_t ns = (kDecodeTargetWaves + units - 1) / units;
-      ns = std::min<int64_t>(ns, kDecodeMaxSplits);
-      ns = std::min<int64_t>(ns, std::max<int64_t>(1, max_key / kDecodeMinSplitKeys));
-      ns = std::min<int64_t>(ns, (int64_t)(ws_bytes / std::max<int64_t>(per_split, 1)));
-      if (ns > 1) {
-        const int32_t kt = attn_decode_keys_per_tile();
-        const int32_t len = cdiv(cdiv(max_key, ns), kt) * kt;
-        a.n_splits = cdiv(max_key, len);
-        a.split_len = len;
+      const int64_t most = std::min<int64_t>(kDecodeMaxSplits, (int64_t)(ws_bytes / std::max<int64_t>(per_split, 1)));
+      // tiles of the shortest split in [lo, hi] whose waves fit (hi: no split)
+      int64_t hi = cdiv(max_key, kt), lo = hi;
+      if (most > 1) lo = std::min(hi, std::max<int64_t>(kDecodeMinSplitKeys / kt, cdiv(cdiv(max_key, most), kt)));
+      while (lo < hi) {
+        const int64_t mid = (lo + hi) / 2;
+        if (waves(mid * kt) <= kDecodeTargetWaves) hi = mid;
+        else lo = mid + 1;
+      }
+      a.n_splits = cdiv(max_key, lo * kt);
+      if (a.n_splits > 1) {
+        a.split_len = (int32_t)(lo * kt);
         a.ws_acc = (float*)ws;
         a.ws_ml = a.ws_acc + (int64_t)a.n_splits * a.n_rows * p->d;
+      }
+      a.n_tiles = 0;                               // waves, and each entry's first
+      for (int32_t i = 0; i < cnt; ++i) {
+        a.e[i].tile_start = a.n_tiles;
+        const int64_t kv = (int64_t)chunk[i].prefix + chunk[i].q_len;
+        a.n_tiles += (a.n_splits > 1 ? cdiv(kv, a.split_len) : 1) * p->hkv;
       }
       hipError_t err = launch_attn_decode(a, p->dtype == PGSR_FP8_E4M3, st);
       if (err == hipSuccess && a.n_splits > 1) err = launch_split_combine(a, false, st);

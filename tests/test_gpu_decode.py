@@ -145,3 +145,25 @@ def test_decode_kernel_multi_token_over_poisoned_tails(case):
             assert np.isfinite(got).all(), f"{name} seq {i}"
             assert_close(got, ref, "bf16", f"{name} seq {i}")
         off += ep.suffix
+
+
+@pytest.mark.parametrize("prefixes,max_splits", [
+    ((63,), 64), ((64,), 64), ((65, 1, 4000), 64),          # one split, the first second split, many beside one
+    ((1330,), 64),                                           # 21 splits: two groups of the combine
+    ((2047,), 3),                                            # the workspace is the limit
+    (tuple(17 + (37 * i) % 900 for i in range(66)), 16),     # two launches, an entry per lane in the first
+])
+def test_decode_splits_of_ragged_sequences(prefixes, max_splits):
+    """Every sequence of a launch is cut at the same length, so into its own
+    number of splits, and waves are numbered through them."""
+    log(f"decode splits n={len(prefixes)} max={max(prefixes)} max_splits={max_splits}")
+    rng = np.random.default_rng(len(prefixes) + prefixes[0])
+    eps = [W.draw_episode(rng, GEOM, "bf16", P, 1, P + 1) for P in prefixes]
+    n = len(eps)
+    pool = make_pool(GEOM, "bf16", sum(_blocks(P + 1) + 1 for P in prefixes), n, _blocks(max(prefixes) + 1) + 1,
+                     split_q=n, max_splits=max_splits)
+    for s, ep in enumerate(eps):
+        _prefill(pool, ep, s)
+    out = _decode(pool, eps, list(range(n)), 1)
+    for s, ep in enumerate(eps):
+        assert_close(out[0, s:s + 1].float().cpu().numpy(), _oracle_step(ep, 0), "bf16", f"seq {s} of {prefixes[s]}")
