@@ -3,14 +3,17 @@
 // stages, tiles from 16 x 16 (one wave, a re-decoded token against a model's
 // weights) to 256 x 128 (eight waves).
 //
-// What bounds it: few rows stream W from HBM once (1 x 4096 x 14336: 23 us,
-// 5.1 TB/s; the register-staged kernel 134 us, because its two K steps in
+// What bounds it: few rows stream W from HBM once (1 x 4096 x 14336: 22 us,
+// 5.3 TB/s; the register-staged kernel 134 us, because its two K steps in
 // flight cover little of the load latency and each step pays an LDS store, a
-// barrier and an LDS read in a row); a hundred rows are bound by LDS (each tile
-// byte is written once and read by every wave that needs it; 102 x 4096 x
-// 14336: 42.6 against 143 us, 33 us of it with W already in L2); from a few
-// hundred rows on the matrix cores (2048 x 4096 x 4096: 62 against 86-91 us,
-// 1110 TFLOP/s; 2048 x 1024 x 4096: 24.5 against 55 us).
+// barrier and an LDS read in a row).  From a few tens of rows on it is the rate
+// at which a CU takes lines that miss L2: the lines in flight are held in the
+// 32 KB first-level cache, so at HBM's latency a CU takes about 59 B/ns, however
+// many requests or waves wait (a copy of the kernel without LDS reads and
+// products takes the same 43 us at 102 x 4096 x 14336, and 30 us with W and X
+// in L2; waves that only load, other wave layouts and deeper rings move
+// nothing).  2048 x 4096 x 4096: 62 against 86-91 us, 1110 TFLOP/s; 2048 x 1024
+// x 4096: 24.5 against 55 us.
 //
 // A stage is KSUB images of 64 k (128-byte rows of X, then of W).  A request
 // is 8 rows x 128 bytes, 1 KB of contiguous LDS with lane l's 16 bytes at byte
@@ -78,11 +81,17 @@ struct DmaArgs {
   int n[kGemmMulti];
 };
 
+// ONCE: one tile row, so no other tile reads this W: non-temporal requests,
+// which pass the first-level cache without taking lines of it (1 x 4096 x
+// 14336: 22.2 against 24.5 us, the gate|up projection 1 x 28672 x 4096 41
+// against 48, 102 x 28672 x 4096 in 128 x 128 tiles 52 against 56).  Where
+// several tile rows share W they cost: the later readers miss L2 too (102 x
+// 4096 x 14336 in 64 x 32 tiles: 49 against 44 us).
 // SILU: W holds n gate rows, then n up rows; a tile takes BN / 2 of each in
 // alternating groups of 16, so a lane holds gate and up of the same outputs
 // (sub-tiles 2 i and 2 i + 1) and stores bf16(SiLU(bf16(gate)) * bf16(up)),
 // the bits of the projection followed by the gated product.
-template <int BM, int BN, int WGM, int WGN, int KSUB, int NST, int GS, int GM, bool SILU>
+template <int BM, int BN, int WGM, int WGN, int KSUB, int NST, int GS, int GM, bool SILU, bool ONCE>
 __global__ void __launch_bounds__(WGM * WGN * 64, 1) gemm_bf16_dma_kernel(DmaArgs a) {
   constexpr int NW = WGM * WGN;
   constexpr int TM = BM / WGM / 16, TN = BN / WGN / 16;
@@ -158,9 +167,14 @@ __global__ void __launch_bounds__(WGM * WGN * 64, 1) gemm_bf16_dma_kernel(DmaArg
     for (int sub = 0; sub < KSUB; ++sub) {
 #pragma unroll
       for (int j = 0; j < WR; ++j)
-        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                     ::"v"(woff[j]), "s"(ws + sub * 2 * kSub), "s"(img + 2u * (sub * SUBE + BM * kSub) + 1024u * NW * j)
-                     : "memory", "m0");
+        if constexpr (ONCE)
+          asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt"
+                       ::"v"(woff[j]), "s"(ws + sub * 2 * kSub), "s"(img + 2u * (sub * SUBE + BM * kSub) + 1024u * NW * j)
+                       : "memory", "m0");
+        else
+          asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                       ::"v"(woff[j]), "s"(ws + sub * 2 * kSub), "s"(img + 2u * (sub * SUBE + BM * kSub) + 1024u * NW * j)
+                       : "memory", "m0");
 #pragma unroll
       for (int j = 0; j < XR; ++j)
         asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
@@ -285,8 +299,11 @@ void launch_dma(const DmaArgs& a, hipStream_t s) {
   int cols = 0;
   for (int i = 0; i < a.count; ++i) cols += (a.n[i] + BNO - 1) / BNO;
   const int tiles = ((a.m + BM - 1) / BM) * cols;
-  hipLaunchKernelGGL((gemm_bf16_dma_kernel<BM, BN, WGM, WGN, KSUB, NST, GS, GM, SILU>), dim3(8 * ((tiles + 7) / 8)),
-                     dim3(WGM * WGN * 64), 0, s, a);
+  const dim3 grid(8 * ((tiles + 7) / 8)), blk(WGM * WGN * 64);
+  if (a.m <= BM)
+    hipLaunchKernelGGL((gemm_bf16_dma_kernel<BM, BN, WGM, WGN, KSUB, NST, GS, GM, SILU, true>), grid, blk, 0, s, a);
+  else
+    hipLaunchKernelGGL((gemm_bf16_dma_kernel<BM, BN, WGM, WGN, KSUB, NST, GS, GM, SILU, false>), grid, blk, 0, s, a);
 }
 
 // Tile choice: the time of a launch is close to
@@ -400,10 +417,13 @@ hipError_t launch_gemm_bf16_silu(int m, int dff, int k, const void* x, const voi
   DmaArgs a{m, k, 1, (const uint16_t*)x, {(const uint16_t*)w}, {nullptr}, {(uint16_t*)y}, {dff}};
   const int n = 2 * dff;
   switch (pick_tile(m, 1, &n, 0, kWide - 1)) {
-    case 0: launch_dma<16, 32, 1, 1, 2, 5, 2, 8, true>(a, s); break;
+    case 0:
     case 1:
     case 2:
-      if (m <= 16) launch_dma<16, 32, 1, 1, 2, 5, 2, 8, true>(a, s);
+      // (14336 outputs x 4096: 42 against 49 us for 30 rows, 40.6 against 41.3
+      // for one; fewer columns leave CUs without a tile of 64)
+      if (n >= 64 * kCus) launch_dma<32, 64, 2, 2, 2, 3, 2, 8, true>(a, s);
+      else if (m <= 16) launch_dma<16, 32, 1, 1, 2, 5, 2, 8, true>(a, s);
       else launch_dma<32, 32, 2, 1, 2, 4, 4, 8, true>(a, s);
       break;
     case 3: launch_dma<64, 32, 4, 1, 2, 6, 2, 8, true>(a, s); break;

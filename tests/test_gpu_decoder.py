@@ -103,7 +103,8 @@ def _dev_weights(ws):
     # one product per tile of the projection with the gate in its epilogue, ragged in rows or columns (a
     # last group of 8), then K = 192 and the 256 x 256 kernel's size, which run as two launches
     (1, 1000, 128), (16, 2048, 640), (17, 1024, 256), (40, 2040, 384), (100, 1496, 1024), (200, 3064, 384),
-    (300, 2048, 896), (700, 2056, 256), (1400, 2040, 128), (9, 96, 192), (4096, 2048, 128)])
+    (300, 2048, 896), (700, 2056, 256), (1400, 2040, 128), (9, 96, 192), (4096, 2048, 128),
+    (1, 8200, 128), (31, 8192, 384)])
 def test_projection_with_gate_equals_two_steps(m, dff, k):
     rng = np.random.default_rng(m + dff)
     x, w = _dev(rng.standard_normal((m, k)) * 2), _dev(rng.standard_normal((2 * dff, k)) * k ** -0.5)
