@@ -132,9 +132,8 @@ struct AppendArgs {
   AppendEntry e[kMaxSeqsPerLaunch];
 };
 
-// Restore + reserve + append in one launch (bf16 pools, no copy-on-write, no
-// poisoning): workgroup (0, 0) takes the crop of `ce` exactly as crop_kernel
-// does, then the reservation pops of `e` from the stack it just pushed to
+// Restore + reserve + append in one launch (no copy-on-write, no poisoning):
+// workgroup (0, 0) takes the crop of `ce` exactly as crop_kernel does, then the reservation pops of `e` from the stack it just pushed to
 // (tables, counts, lengths, top); the other workgroups copy the K/V of item
 // blockIdx.x - 1 and KV head blockIdx.y into block ids[item], which the host
 // mirror computed by the same steps.
@@ -154,6 +153,7 @@ struct FusedAppendArgs {
   int32_t* chk;
   int32_t max_bps, n_blocks, n_kv_heads, block_size, head_dim, layer;
   int32_t commit;
+  float k_scale, v_scale;   // FP8 cache
   int32_t top_before;  // stack height before the crop
   int32_t top_after;   // after the reservation
   int32_t n_crop;
@@ -236,7 +236,7 @@ hipError_t launch_append(const AppendArgs& a, int elem_bytes, hipStream_t s);
 // False when the fused launch does not cover this geometry (the caller then
 // launches crop and append separately).
 bool fused_append_supported(int block_size, int head_dim);
-hipError_t launch_fused_append(const FusedAppendArgs& a, hipStream_t s);
+hipError_t launch_fused_append(const FusedAppendArgs& a, int elem_bytes, hipStream_t s);
 hipError_t launch_attn_f32(const AttnArgs& a, hipStream_t s);
 hipError_t launch_attn_bf16(const AttnArgs& a, hipStream_t s);
 // Software-pipelined prefill for head_dim 128, bf16 and FP8 pools: 32 query

@@ -12,6 +12,8 @@
 // written for clarity and coalescing, not occupancy.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "internal.h"
 
 namespace pgsr {
@@ -185,90 +187,6 @@ __device__ inline uint8_t to_cache<uint16_t, uint8_t>(uint16_t x, float scale) {
   return e4m3_code(__uint_as_float((uint32_t)x << 16) / scale);
 }
 
-// Reserve + append.  blockIdx.x enumerates (sequence, logical block) items,
-// blockIdx.y the KV head.  The physical id of a newly reserved logical block
-// lb is read straight from the stack (free_list[stack_before - 1 - k] for the
-// k-th new block of the sequence), so no workgroup depends on another's table
-// write; the kv-head-0 workgroup records it in the table.
-//   K: token p -> k_cache[layer][id][h][p % B][:]      (row copy)
-//   V: token p -> v_cache[layer][id][h][:][p % B]      (transposed via LDS)
-template <typename TI, typename T>
-__global__ void __launch_bounds__(256) append_kernel(AppendArgs a) {
-  // [slot][d] staging of V, rows padded by 8 elements on the 16-byte path
-  // (block_size <= 64, head_dim <= 128)
-  __shared__ __attribute__((aligned(16))) T vstage[64 * (128 + 8)];
-  const int item = blockIdx.x;
-  int ei = 0;
-  while (ei + 1 < a.n && a.e[ei + 1].item_start <= item) ++ei;
-  const AppendEntry e = a.e[ei];
-  const int B = a.block_size, D = a.head_dim, h = blockIdx.y;
-  const int32_t lb = e.lb_first + (item - e.item_start);
-  int32_t* row = a.tables + (int64_t)e.seq * a.max_bps;
-  const int32_t cow_pops = e.cow_old >= 0 ? 1 : 0;   // cow_kernel took the first pop
-  int32_t id;
-  if (lb < e.nalloc_before) {
-    id = blk_id(row[lb], a.n_blocks, a.chk);
-  } else {
-    id = blk_id(a.free_list[e.stack_before - 1 - cow_pops - (lb - e.nalloc_before)], a.n_blocks, a.chk);
-    if (h == 0 && threadIdx.x == 0) {
-      row[lb] = id;
-      a.refs[id] = 1;
-    }
-  }
-  if (threadIdx.x == 0 && h == 0) {
-    if (a.commit && item == e.item_start) a.lens[e.seq] = e.prefix + e.q_len;
-    if (a.write_top && item == 0) *a.free_top = a.top_after;
-  }
-  const int32_t p0 = max(e.prefix, lb * B);
-  const int32_t p1 = min(e.prefix + e.q_len, (lb + 1) * B);
-  const int nt = p1 - p0;  // tokens landing in this block (>= 1)
-  const int s0 = p0 - lb * B;
-  const int64_t blk = ((int64_t)a.layer * a.n_blocks + id) * a.n_kv_heads + h;
-  const TI* kin = (const TI*)a.k_in;
-  const TI* vin = (const TI*)a.v_in;
-  T* kc = (T*)a.k_cache + blk * B * D;
-  T* vc = (T*)a.v_cache + blk * D * B;
-  if constexpr (sizeof(TI) == 2 && sizeof(T) == 2) {
-    // bf16 pool, span starting and ending on 8-slot boundaries: K rows move in
-    // 16-byte chunks; V is staged [slot][d] (rows padded to D + 8, so the
-    // transposing reads of 8 slots at one d fall in distinct banks) and each
-    // d row's 8-slot runs are written as 16-byte chunks.
-    if ((s0 & 7) == 0 && (nt & 7) == 0 && (D & 7) == 0) {
-      typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-      const int C8 = D / 8, DP = D + 8, S8 = nt / 8;
-      const int64_t row_stride = (int64_t)a.n_kv_heads * D;
-      const int64_t src0 = ((int64_t)(e.q_off + (p0 - e.prefix)) * a.n_kv_heads + h) * D;
-      for (int i = threadIdx.x; i < nt * C8; i += blockDim.x) {
-        const int t = i / C8, c = (i % C8) * 8;
-        const int64_t src = src0 + t * row_stride + c;
-        *(u4*)(kc + (int64_t)(s0 + t) * D + c) = *(const u4*)((const TI*)a.k_in + src);
-        *(u4*)(&vstage[t * DP + c]) = *(const u4*)((const TI*)a.v_in + src);
-      }
-      __syncthreads();
-      for (int i = threadIdx.x; i < D * S8; i += blockDim.x) {
-        const int d = i / S8, t0 = (i % S8) * 8;
-        u4 out;
-#pragma unroll
-        for (int w = 0; w < 4; ++w)
-          out[w] = (uint32_t)vstage[(t0 + 2 * w) * DP + d] | ((uint32_t)vstage[(t0 + 2 * w + 1) * DP + d] << 16);
-        *(u4*)(vc + (int64_t)d * B + s0 + t0) = out;
-      }
-      return;
-    }
-  }
-  for (int i = threadIdx.x; i < nt * D; i += blockDim.x) {
-    const int t = i / D, c = i % D;
-    const int64_t src = ((int64_t)(e.q_off + (p0 - e.prefix) + t) * a.n_kv_heads + h) * D + c;
-    kc[(int64_t)(s0 + t) * D + c] = to_cache<TI, T>(kin[src], a.k_scale);
-    vstage[t * D + c] = to_cache<TI, T>(vin[src], a.v_scale);
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < nt * D; i += blockDim.x) {
-    const int c = i / nt, t = i % nt;
-    vc[(int64_t)c * B + s0 + t] = vstage[t * D + c];
-  }
-}
-
 // K/V of the tokens of one (sequence, logical block) item for one KV head,
 // bf16 pools, one wave: tokens p0 .. p0+nt-1 (block slots s0 .. s0+nt-1) from
 // the packed inputs (rows of n_kv_heads * D elements) into the block-head at
@@ -277,6 +195,11 @@ __global__ void __launch_bounds__(256) append_kernel(AppendArgs a) {
 // V is staged [slot][d] in LDS (rows padded to D + 8) and written back along d
 // rows: 16-byte runs of 8 slots when the span starts and ends on 8-slot
 // boundaries, else slot by slot (the partial first and last blocks).
+template <typename T>
+constexpr int kStagePad = sizeof(T) == 4 ? 4 : 8;   // elements; rows stay on chunk boundaries
+template <typename TI, typename T>
+constexpr int kAppendThreads = sizeof(TI) == sizeof(T) ? 64 : 256;
+
 template <int B, int D>
 __device__ inline void copy_block_head(const uint16_t* __restrict__ kin, const uint16_t* __restrict__ vin,
                                        int64_t row_stride, uint16_t* __restrict__ kc,
@@ -353,13 +276,100 @@ __device__ inline void copy_block_head(const uint16_t* __restrict__ kin, const u
   }
 }
 
-// Reserve + append for bf16 pools: one wave per (sequence, logical block) item
-// and KV head; block ids read from the table or straight from the stack
+// The same for fp32 pools and for FP8 caches fed from bf16 (each value the code
+// of fp32(x / scale)).  Inputs on 16-byte boundaries move in 16-byte chunks, all
+// loads of a round ahead of its stores, V back in runs of 4 (fp32) or 8 slots;
+// others element by element, and so do codes where the chunks would leave
+// threads idle (a division and the rounding per element, not the accesses, are
+// what a code costs; hence four waves).  With the crop in the same launch: 640
+// fp32 tokens restored and 128 replayed 20.7 -> 17.6 us a call, 2048 FP8 tokens
+// on 8189 about 5 of 300 us.
+template <typename TI, typename T, int B, int D>
+__device__ inline void copy_span(const TI* __restrict__ kin, const TI* __restrict__ vin, int64_t row_stride,
+                                 T* __restrict__ kc, T* __restrict__ vc, int s0, int nt, float k_scale,
+                                 float v_scale, T* vstage) {
+  constexpr int E = 16 / sizeof(TI), C = D / E, R = sizeof(T) == 4 ? 4 : 8;
+  constexpr int DP = D + kStagePad<T>, NT = kAppendThreads<TI, T>, J = NT == 64 ? 4 : 2;
+  typedef TI in_t __attribute__((ext_vector_type(E)));
+  typedef T chunk_t __attribute__((ext_vector_type(E)));
+  typedef T run_t __attribute__((ext_vector_type(R)));
+  const int lane = threadIdx.x;
+  const int nck = nt * C;
+  if ((((uintptr_t)kin | (uintptr_t)vin) & 15) == 0 && (sizeof(TI) == sizeof(T) || nck >= NT)) {
+    for (int i0 = 0; i0 < nck; i0 += J * NT) {
+      in_t kk[J], vv[J];
+#pragma unroll
+      for (int j = 0; j < J; ++j) {
+        const int i = i0 + j * NT + lane;
+        if (i < nck) {
+          const int64_t off = (i / C) * row_stride + (i % C) * E;
+          kk[j] = *(const in_t*)(kin + off);
+          vv[j] = *(const in_t*)(vin + off);
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < J; ++j) {
+        const int i = i0 + j * NT + lane;
+        if (i < nck) {
+          const int t = i / C, c = (i % C) * E;
+          chunk_t ko, vo;
+#pragma unroll
+          for (int x = 0; x < E; ++x) {
+            ko[x] = to_cache<TI, T>(kk[j][x], k_scale);
+            vo[x] = to_cache<TI, T>(vv[j][x], v_scale);
+          }
+          *(chunk_t*)(kc + (int64_t)(s0 + t) * D + c) = ko;
+          *(chunk_t*)(&vstage[t * DP + c]) = vo;
+        }
+      }
+    }
+  } else {
+    for (int i = lane; i < nt * D; i += NT) {
+      const int t = i / D, c = i % D;
+      const int64_t off = t * row_stride + c;
+      kc[(int64_t)(s0 + t) * D + c] = to_cache<TI, T>(kin[off], k_scale);
+      vstage[t * DP + c] = to_cache<TI, T>(vin[off], v_scale);
+    }
+  }
+  __syncthreads();
+  if (s0 % R == 0 && nt % R == 0) {
+    const int runs = nt / R;
+    for (int i = lane; i < D * runs; i += NT) {
+      const int d = i / runs, t0 = (i % runs) * R;
+      run_t out;
+#pragma unroll
+      for (int x = 0; x < R; ++x) out[x] = vstage[(t0 + x) * DP + d];
+      *(run_t*)(vc + (int64_t)d * B + s0 + t0) = out;
+    }
+  } else {
+    for (int t = 0; t < nt; ++t)
+#pragma unroll
+      for (int d = lane; d < D; d += NT) vc[(int64_t)d * B + s0 + t] = vstage[t * DP + d];
+  }
+}
+
+// One item's copy for one KV head, by the pool's types.
+template <typename TI, typename T, int B, int D>
+__device__ inline void copy_item(const void* k_in, const void* v_in, void* k_cache, void* v_cache, int64_t src0,
+                                 int64_t row_stride, int64_t blk, int s0, int nt, float k_scale, float v_scale,
+                                 T* vstage) {
+  const TI *kin = (const TI*)k_in + src0, *vin = (const TI*)v_in + src0;
+  T *kc = (T*)k_cache + blk * B * D, *vc = (T*)v_cache + blk * D * B;
+  if constexpr (sizeof(TI) == 2 && sizeof(T) == 2)
+    copy_block_head<B, D>(kin, vin, row_stride, kc, vc, s0, nt, vstage);
+  else
+    copy_span<TI, T, B, D>(kin, vin, row_stride, kc, vc, s0, nt, k_scale, v_scale, vstage);
+}
+
+// Reserve + append: one wave (FP8: four) per (sequence, logical block) item and
+// KV head; block ids read from the table or straight from the stack
 // (free_list[stack_before - 1 - k] for the k-th new block of the sequence), so
 // no workgroup depends on another's table write.
-template <int B, int D>
-__global__ void __launch_bounds__(64) append_bf16_kernel(AppendArgs a) {
-  __shared__ __attribute__((aligned(16))) uint16_t vstage[B * (D + 8)];
+//   K: token p -> k_cache[layer][id][h][p % B][:]      (row copy)
+//   V: token p -> v_cache[layer][id][h][:][p % B]      (transposed via LDS)
+template <typename TI, typename T, int B, int D>
+__global__ void __launch_bounds__((kAppendThreads<TI, T>)) append_kernel(AppendArgs a) {
+  __shared__ __attribute__((aligned(16))) T vstage[B * (D + kStagePad<T>)];
   const int item = blockIdx.x, lane = threadIdx.x;
   int ei = 0;
   while (ei + 1 < a.n && a.e[ei + 1].item_start <= item) ++ei;
@@ -385,9 +395,8 @@ __global__ void __launch_bounds__(64) append_bf16_kernel(AppendArgs a) {
   const int64_t row_stride = (int64_t)a.n_kv_heads * D;
   const int64_t src0 = ((int64_t)(e.q_off + (p0 - e.prefix)) * a.n_kv_heads + h) * D;
   const int64_t blk = ((int64_t)a.layer * a.n_blocks + id) * a.n_kv_heads + h;
-  copy_block_head<B, D>((const uint16_t*)a.k_in + src0, (const uint16_t*)a.v_in + src0, row_stride,
-                        (uint16_t*)a.k_cache + blk * B * D, (uint16_t*)a.v_cache + blk * D * B,
-                        p0 - lb * B, p1 - p0, vstage);
+  copy_item<TI, T, B, D>(a.k_in, a.v_in, a.k_cache, a.v_cache, src0, row_stride, blk, p0 - lb * B, p1 - p0,
+                         a.k_scale, a.v_scale, vstage);
 }
 
 // Restore + reserve + append in one launch.  Workgroup (0, 0) runs the crop of
@@ -399,12 +408,12 @@ __global__ void __launch_bounds__(64) append_bf16_kernel(AppendArgs a) {
 // stack top; its accesses are ordered by the barriers between rounds.  Every
 // other workgroup copies one item's K/V for one KV head into ids[item] and
 // touches no metadata.
-template <int B, int D>
-__global__ void __launch_bounds__(64) fused_append_kernel(FusedAppendArgs a) {
-  __shared__ __attribute__((aligned(16))) uint16_t vstage[B * (D + 8)];
+template <typename TI, typename T, int B, int D>
+__global__ void __launch_bounds__((kAppendThreads<TI, T>)) fused_append_kernel(FusedAppendArgs a) {
+  __shared__ __attribute__((aligned(16))) T vstage[B * (D + kStagePad<T>)];
   const int lane = threadIdx.x, h = blockIdx.y;
   if (blockIdx.x == 0) {
-    if (h != 0) return;
+    if (h != 0 || lane >= 64) return;            // one wave
     // 256 entries per round, entry j0 + 64 r + lane in lane's slot r, so the
     // ascending push order is r-major: position = pushes of slots before r
     // plus pushes of lower lanes in slot r.
@@ -473,9 +482,8 @@ __global__ void __launch_bounds__(64) fused_append_kernel(FusedAppendArgs a) {
   const int64_t row_stride = (int64_t)a.n_kv_heads * D;
   const int64_t src0 = ((int64_t)(e.q_off + (p0 - e.prefix)) * a.n_kv_heads + h) * D;
   const int64_t blk = ((int64_t)a.layer * a.n_blocks + a.ids[item]) * a.n_kv_heads + h;
-  copy_block_head<B, D>((const uint16_t*)a.k_in + src0, (const uint16_t*)a.v_in + src0, row_stride,
-                        (uint16_t*)a.k_cache + blk * B * D, (uint16_t*)a.v_cache + blk * D * B,
-                        p0 - lb * B, p1 - p0, vstage);
+  copy_item<TI, T, B, D>(a.k_in, a.v_in, a.k_cache, a.v_cache, src0, row_stride, blk, p0 - lb * B, p1 - p0,
+                         a.k_scale, a.v_scale, vstage);
 }
 
 }  // namespace
@@ -517,52 +525,63 @@ hipError_t launch_poison(const PoisonArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+namespace {
+
+// f(B, D) as integral constants for the geometry; false where there is none
+template <class F>
+bool with_geometry(int block_size, int head_dim, F&& f) {
+  auto by_dim = [&](auto b) {
+    if (head_dim == 128) f(b, std::integral_constant<int, 128>{});
+    else if (head_dim == 64) f(b, std::integral_constant<int, 64>{});
+    else return false;
+    return true;
+  };
+  switch (block_size) {
+    case 16: return by_dim(std::integral_constant<int, 16>{});
+    case 32: return by_dim(std::integral_constant<int, 32>{});
+    case 64: return by_dim(std::integral_constant<int, 64>{});
+    default: return false;
+  }
+}
+
+template <typename TI, typename T>
+hipError_t append_of(const AppendArgs& a, bool any_cow, hipStream_t s) {
+  if (any_cow) hipLaunchKernelGGL(cow_kernel<T>, dim3(a.n, a.n_kv_heads), dim3(256), 0, s, a);
+  const bool ok = with_geometry(a.block_size, a.head_dim, [&](auto b, auto d) {
+    hipLaunchKernelGGL((append_kernel<TI, T, decltype(b)::value, decltype(d)::value>),
+                       dim3(a.n_items, a.n_kv_heads), dim3(kAppendThreads<TI, T>), 0, s, a);
+  });
+  return ok ? hipGetLastError() : hipErrorInvalidValue;
+}
+
+template <typename TI, typename T>
+hipError_t fused_append_of(const FusedAppendArgs& a, hipStream_t s) {
+  const bool ok = with_geometry(a.block_size, a.head_dim, [&](auto b, auto d) {
+    hipLaunchKernelGGL((fused_append_kernel<TI, T, decltype(b)::value, decltype(d)::value>),
+                       dim3(1 + a.n_items, a.n_kv_heads), dim3(kAppendThreads<TI, T>), 0, s, a);
+  });
+  return ok ? hipGetLastError() : hipErrorInvalidValue;
+}
+
+}  // namespace
+
 hipError_t launch_append(const AppendArgs& a, int elem_bytes, hipStream_t s) {
   if (a.n <= 0 || a.n_items <= 0) return hipSuccess;
   bool any_cow = false;
   for (int i = 0; i < a.n; ++i) any_cow |= a.e[i].cow_old >= 0;
-  const dim3 cow_grid(a.n, a.n_kv_heads), grid(a.n_items, a.n_kv_heads);
-  if (elem_bytes == 4) {
-    if (any_cow) hipLaunchKernelGGL(cow_kernel<uint32_t>, cow_grid, dim3(256), 0, s, a);
-    hipLaunchKernelGGL((append_kernel<uint32_t, uint32_t>), grid, dim3(256), 0, s, a);
-  } else if (elem_bytes == 2) {
-    if (any_cow) hipLaunchKernelGGL(cow_kernel<uint16_t>, cow_grid, dim3(256), 0, s, a);
-    if (a.head_dim == 128 && a.block_size == 16)
-      hipLaunchKernelGGL((append_bf16_kernel<16, 128>), grid, dim3(64), 0, s, a);
-    else if (a.head_dim == 128 && a.block_size == 32)
-      hipLaunchKernelGGL((append_bf16_kernel<32, 128>), grid, dim3(64), 0, s, a);
-    else if (a.head_dim == 128 && a.block_size == 64)
-      hipLaunchKernelGGL((append_bf16_kernel<64, 128>), grid, dim3(64), 0, s, a);
-    else if (a.head_dim == 64 && a.block_size == 16)
-      hipLaunchKernelGGL((append_bf16_kernel<16, 64>), grid, dim3(64), 0, s, a);
-    else if (a.head_dim == 64 && a.block_size == 32)
-      hipLaunchKernelGGL((append_bf16_kernel<32, 64>), grid, dim3(64), 0, s, a);
-    else if (a.head_dim == 64 && a.block_size == 64)
-      hipLaunchKernelGGL((append_bf16_kernel<64, 64>), grid, dim3(64), 0, s, a);
-    else
-      hipLaunchKernelGGL((append_kernel<uint16_t, uint16_t>), grid, dim3(256), 0, s, a);
-  } else {                                          // FP8 cache, bf16 inputs
-    if (any_cow) hipLaunchKernelGGL(cow_kernel<uint8_t>, cow_grid, dim3(256), 0, s, a);
-    hipLaunchKernelGGL((append_kernel<uint16_t, uint8_t>), grid, dim3(256), 0, s, a);
-  }
-  return hipGetLastError();
+  return elem_bytes == 4   ? append_of<uint32_t, uint32_t>(a, any_cow, s)
+         : elem_bytes == 2 ? append_of<uint16_t, uint16_t>(a, any_cow, s)
+                           : append_of<uint16_t, uint8_t>(a, any_cow, s);   // FP8 cache, bf16 inputs
 }
 
 bool fused_append_supported(int block_size, int head_dim) {
-  return (head_dim == 128 || head_dim == 64) && (block_size == 16 || block_size == 32 || block_size == 64);
+  return with_geometry(block_size, head_dim, [](auto, auto) {});
 }
 
-hipError_t launch_fused_append(const FusedAppendArgs& a, hipStream_t s) {
-  const dim3 grid(1 + a.n_items, a.n_kv_heads);
-#define PGSR_FUSED(BS, HD)                                                                      \
-  if (a.block_size == BS && a.head_dim == HD) {                                                  \
-    hipLaunchKernelGGL((fused_append_kernel<BS, HD>), grid, dim3(64), 0, s, a);                  \
-    return hipGetLastError();                                                                    \
-  }
-  PGSR_FUSED(16, 128) PGSR_FUSED(32, 128) PGSR_FUSED(64, 128)
-  PGSR_FUSED(16, 64) PGSR_FUSED(32, 64) PGSR_FUSED(64, 64)
-#undef PGSR_FUSED
-  return hipErrorInvalidValue;
+hipError_t launch_fused_append(const FusedAppendArgs& a, int elem_bytes, hipStream_t s) {
+  return elem_bytes == 4   ? fused_append_of<uint32_t, uint32_t>(a, s)
+         : elem_bytes == 2 ? fused_append_of<uint16_t, uint16_t>(a, s)
+                           : fused_append_of<uint16_t, uint8_t>(a, s);
 }
 
 }  // namespace pgsr

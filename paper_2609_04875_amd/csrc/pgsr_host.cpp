@@ -359,6 +359,8 @@ int do_replay(pgsr_pool* p, int32_t layer, int32_t n, const int32_t* seqs,
     a.head_dim = p->d;
     a.layer = layer;
     a.commit = commit ? 1 : 0;
+    a.k_scale = p->k_scale[layer];
+    a.v_scale = p->v_scale[layer];
     a.top_before = fold->top_before;
     a.n_crop = fold->n;
     std::memcpy(a.ce, fold->e, sizeof(CropEntry) * fold->n);
@@ -388,7 +390,7 @@ int do_replay(pgsr_pool* p, int32_t layer, int32_t n, const int32_t* seqs,
     }
     a.n_items = items;
     a.top_after = p->h_top;
-    hipError_t err = launch_fused_append(a, st);
+    hipError_t err = launch_fused_append(a, eb, st);
     if (err != hipSuccess) return hip_fail(err, "restore + append launch");
   }
   // Reserve + append, chunked; the mirror takes the same pops in call order.
@@ -645,7 +647,7 @@ int do_replay(pgsr_pool* p, int32_t layer, int32_t n, const int32_t* seqs,
 // Restore (crop seqs[i] to crop_lens[i]; none when crop_lens is null) then the
 // replay of q_lens on `layer`, validated together on the mirror before anything
 // is launched.  The crop's device work rides in the append launch when that
-// launch covers it: a bf16 pool with a fused kernel for its geometry, at most
+// launch covers it: a fused kernel for the pool's geometry, at most
 // kMaxFusedSeqs sequences and kMaxFusedItems appended blocks, every sequence
 // with work, and no kept partial tail block named by another row (so no
 // copy-on-write).  Otherwise the crop is its own launch first.
@@ -674,7 +676,7 @@ int restore_replay(pgsr_pool* p, int32_t layer, int32_t n, const int32_t* seqs,
   if (!crop_lens || n == 0)
     return do_replay(p, layer, n, seqs, q_lens, q, k, v, o, scale, flags, recomputed, p->workspace,
                      p->workspace_bytes, st);
-  bool fold = p->dtype == PGSR_BF16 && fused_append_supported(p->B, p->d) && n <= kMaxFusedSeqs;
+  bool fold = fused_append_supported(p->B, p->d) && n <= kMaxFusedSeqs;
   int64_t items = 0;
   for (int32_t i = 0; fold && i < n; ++i) {
     const int32_t L = crop_lens[i], S = q_lens[i];

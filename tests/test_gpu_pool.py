@@ -221,3 +221,52 @@ def test_restore_replay_equals_crop_then_replay(P, S, Tc, B):
     ref = oracle_suffix(ep, scale, rows=rows)
     got = outs[0].reshape(-1, 128)[torch.from_numpy(rows).cuda()].float().cpu().numpy()
     assert_close(got, ref, "bf16", "restore + replay")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "fp8"])
+@pytest.mark.parametrize("B,D,P,S", [(16, 128, 70, 45), (16, 64, 16, 16), (32, 128, 33, 100), (64, 64, 5, 130),
+                                     (64, 128, 100, 1)])
+def test_fp32_and_fp8_append_types(dtype, B, D, P, S):
+    """fp32 and FP8 pools: what restore + replay in one call and in two leave in
+    the cache, the second with K and V off the 16-byte boundaries (element by
+    element): the inputs' bits, or their codes."""
+    from paper_2609_04875_amd import F32, FP8_E4M3, KVPool
+    log(f"append {dtype} B={B} D={D} P={P} S={S}")
+    g = torch.Generator(device="cuda").manual_seed(P + S)
+    hq, hkv, tc = 4, 2, P + 2 * B + 3
+    element = torch.float32 if dtype == "f32" else torch.bfloat16
+    new = lambda n, h: (3 * torch.randn(n, h, D, device="cuda", generator=g)).to(element)  # noqa: E731
+    scale = torch.tensor(0.0125, device="cuda")
+
+    def stored(x):
+        if dtype == "f32":
+            return x.view(torch.int32)
+        return (x.float() / scale).clamp(-448, 448).to(torch.float8_e4m3fn).view(torch.uint8)
+
+    def shifted(x):
+        flat = torch.empty(x.numel() + 1, dtype=x.dtype, device="cuda")
+        flat[1:] = x.reshape(-1)
+        return flat[1:].view(x.shape)
+
+    q0, k0, v0, q, k, v = new(tc, hq), new(tc, hkv), new(tc, hkv), new(S, hq), new(S, hkv), new(S, hkv)
+    states, outs = [], []
+    for one_call in (True, False):
+        pool = KVPool(1, hq, hkv, D, 64, 1, 40, F32 if dtype == "f32" else FP8_E4M3, B)
+        if dtype == "fp8":
+            pool.set_kv_scales([scale.item()], [scale.item()])
+        assert pool.replay(0, [0], [tc], q0, k0, v0, torch.empty_like(q0), D ** -0.5) == 0
+        o = torch.empty_like(q)
+        if one_call:
+            assert pool.restore_replay(0, [0], [P], [S], q, k, v, o, D ** -0.5) == 0
+        else:
+            assert pool.crop([0], [P]) == 0
+            assert pool.replay(0, [0], [S], q, shifted(k), shifted(v), o, D ** -0.5) == 0
+        kc, vc = logical_kv(pool, 0, 0, P + S)
+        raw = torch.int32 if dtype == "f32" else torch.uint8
+        assert torch.equal(kc.contiguous().view(raw), torch.cat([stored(k0[:P]), stored(k)])), one_call
+        assert torch.equal(vc.contiguous().view(raw), torch.cat([stored(v0[:P]), stored(v)])), one_call
+        states.append(pool.state())
+        outs.append(o)
+    for key in states[0]:
+        assert np.array_equal(np.asarray(states[0][key]), np.asarray(states[1][key])), key
+    assert torch.equal(outs[0], outs[1])
