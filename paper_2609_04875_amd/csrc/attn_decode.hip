@@ -128,12 +128,19 @@ attn_decode_kernel(AttnArgs a, const int32_t* __restrict__ tables, const uint16_
 #pragma unroll
     for (int c = 0; c < NK; ++c) kr[c] = *(const u32x4*)(kp + c * EK);
   };
+  // Non-temporal where one instruction takes whole lines (FP8, 16 slots: 32
+  // rows of 16 bytes in a run), which then pass the first-level cache without
+  // taking lines of it: 32 ragged sequences 112.7 against 126.2 us (5.3 TB/s),
+  // 48 x 4000 keys 82 against 97.  K, and V in longer rows, reach a line in
+  // several instructions and lose (K: 155 us, bf16 303 against 190).
   auto load_v = [&](int kb, int idv) {
     const auto* vp = vc + ((head_base + (int64_t)idv * hkv) * D + r) * B + v_key(kb) % B;
 #pragma unroll
     for (int c = 0; c < NV; ++c) {
       const int db = F8 ? c : c / 2, ks = F8 ? 0 : c % 2;
-      vr[c] = *(const u32x4*)(vp + (int64_t)db * 32 * B + 8 * ks);
+      const u32x4* at = (const u32x4*)(vp + (int64_t)db * 32 * B + 8 * ks);
+      if constexpr (F8 && B == 16) vr[c] = __builtin_nontemporal_load(at);
+      else vr[c] = *at;
     }
   };
   auto k_operand = [&](const u32x4 (&k)[NK], int ds) {
