@@ -380,8 +380,9 @@ attn_bf16_kernel(AttnArgs a, const int32_t* __restrict__ tables, const uint16_t*
 // summed in increasing s.  16 threads per row, 8 columns each.  The partials
 // are read kGroup splits at a time, all loads of a group issued before any is
 // used, so a row with many splits (a decode step) waits on few round trips;
-// the sums still run in increasing s.  Groups of 16 where a launch has more
-// than 8 splits (a short decode step has about 20: two round trips, not three).
+// the sums still run in increasing s.  Decode steps with more than 8 splits
+// take groups of 16 (a short one has about 20: two round trips, not three);
+// the others, with more rows and 9 or 10 splits, lose 0.4 us by them.
 template <int D, int kGroup, typename TO>
 __global__ void __launch_bounds__(256) split_combine_kernel(AttnArgs a, TO* __restrict__ og) {
   constexpr int TPR = D / 8;                       // threads per row
@@ -493,12 +494,12 @@ static hipError_t launch_d(const AttnArgs& a, hipStream_t s) {
 }
 
 template <int D, typename TO>
-static void run_combine(const AttnArgs& a, dim3 grid, int threads, hipStream_t s) {
-  if (a.n_splits <= 8) hipLaunchKernelGGL((split_combine_kernel<D, 8, TO>), grid, dim3(threads), 0, s, a, (TO*)a.o);
+static void run_combine(const AttnArgs& a, int group, dim3 grid, int threads, hipStream_t s) {
+  if (group <= 8 || a.n_splits <= 8) hipLaunchKernelGGL((split_combine_kernel<D, 8, TO>), grid, dim3(threads), 0, s, a, (TO*)a.o);
   else hipLaunchKernelGGL((split_combine_kernel<D, 16, TO>), grid, dim3(threads), 0, s, a, (TO*)a.o);
 }
 
-hipError_t launch_split_combine(const AttnArgs& a, bool f32_out, hipStream_t s) {
+hipError_t launch_split_combine(const AttnArgs& a, bool f32_out, int group, hipStream_t s) {
   if (a.row_begin < 0 || a.row_end > a.n_rows) return hipErrorInvalidValue;
   if (a.row_end <= a.row_begin) return hipSuccess;
   // 256 threads per block, or 64 when that would leave CUs idle (decode
@@ -509,11 +510,11 @@ hipError_t launch_split_combine(const AttnArgs& a, bool f32_out, hipStream_t s) 
   const int rows_per_block = threads / tpr;
   dim3 grid((rows + rows_per_block - 1) / rows_per_block);
   if (a.head_dim == 128) {
-    if (f32_out) run_combine<128, float>(a, grid, threads, s);
-    else run_combine<128, uint16_t>(a, grid, threads, s);
+    if (f32_out) run_combine<128, float>(a, group, grid, threads, s);
+    else run_combine<128, uint16_t>(a, group, grid, threads, s);
   } else if (a.head_dim == 64) {
-    if (f32_out) run_combine<64, float>(a, grid, threads, s);
-    else run_combine<64, uint16_t>(a, grid, threads, s);
+    if (f32_out) run_combine<64, float>(a, group, grid, threads, s);
+    else run_combine<64, uint16_t>(a, group, grid, threads, s);
   } else {
     return hipErrorInvalidValue;
   }

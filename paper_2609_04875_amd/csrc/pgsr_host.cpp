@@ -562,7 +562,7 @@ int do_replay(pgsr_pool* p, int32_t layer, int32_t n, const int32_t* seqs,
         a.n_tiles += (a.n_splits > 1 ? cdiv(kv, a.split_len) : 1) * p->hkv;
       }
       hipError_t err = launch_attn_decode(a, p->dtype == PGSR_FP8_E4M3, st);
-      if (err == hipSuccess && a.n_splits > 1) err = launch_split_combine(a, false, st);
+      if (err == hipSuccess && a.n_splits > 1) err = launch_split_combine(a, false, 16, st);
       if (err != hipSuccess) return hip_fail(err, "decode attention launch");
       continue;
     }
@@ -595,18 +595,22 @@ int do_replay(pgsr_pool* p, int32_t layer, int32_t n, const int32_t* seqs,
     // FP8, 1024 tokens: pipelined with four waves 178, four-wave 209, pipelined
     // with eight 236; 2048 tokens: 346, 316 and 297.  Pools that the wide kernel
     // does not take (32- and 64-token blocks): four-wave, then pipelined.
+    // Split bf16 calls with groups that do not divide 32 were cut for the
+    // four-wave kernel, two workgroups to a CU, and keep it (28 / 4 heads, 3 x
+    // 126 tokens on 1600: 38.7 us, wide 50.7; 400 tokens on 900, narrow 35.4
+    // against 31.2).
     auto fits = [&](int tokens) { return count_tiles(tokens) * p->hkv * a.n_splits <= kCus; };
     int narrow = 0, pipe = 0;       // waves per workgroup of the kernel taken
     bool wide = false;
     if (p->dtype == PGSR_F32) {
       set_tiles(attn_f32_tile_tokens(p->d, group));
-    } else if (wide_ok) {
+    } else if (wide_ok && (split_as_wide || a.n_splits == 1)) {
       narrow = fits(attn_bf16_narrow_tile_tokens(group, 2))   ? 2
                : fits(attn_bf16_narrow_tile_tokens(group, 4)) ? 4
                                                               : 0;
       wide = narrow == 0;
       set_tiles(wide ? attn_bf16_pipe_tile_tokens(group, 8) : attn_bf16_narrow_tile_tokens(group, narrow));
-    } else if (pipe_ok) {
+    } else if (pipe_ok && (f8 || split_as_wide || a.n_splits == 1)) {
       const bool few = p->prefill_kind == PGSR_PREFILL_AUTO && fits(attn_bf16_pipe_tile_tokens(group, 4));
       pipe = !few ? 8 : f8 ? 4 : 0;
       set_tiles(pipe ? attn_bf16_pipe_tile_tokens(group, pipe) : attn_bf16_tile_tokens(p->d, group));
@@ -624,7 +628,7 @@ int do_replay(pgsr_pool* p, int32_t layer, int32_t n, const int32_t* seqs,
                      : pipe               ? launch_attn_bf16_pipe(a, pipe, f8, st)
                      : f8                 ? launch_attn_fp8(a, st)
                                           : launch_attn_bf16(a, st);
-    if (err == hipSuccess && a.n_splits > 1) err = launch_split_combine(a, p->dtype == PGSR_F32, st);
+    if (err == hipSuccess && a.n_splits > 1) err = launch_split_combine(a, p->dtype == PGSR_F32, 8, st);
     if (err != hipSuccess) return hip_fail(err, "attention launch");
   }
 
