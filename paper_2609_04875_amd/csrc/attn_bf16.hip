@@ -380,8 +380,9 @@ attn_bf16_kernel(AttnArgs a, const int32_t* __restrict__ tables, const uint16_t*
 // summed in increasing s.  16 threads per row, 8 columns each.  The partials
 // are read kGroup splits at a time, all loads of a group issued before any is
 // used, so a row with many splits (a decode step) waits on few round trips;
-// the sums still run in increasing s.  Decode steps with more than 8 splits
-// take groups of 16 (a short one has about 20: two round trips, not three);
+// the sums still run in increasing s.  Decode steps and fp32 calls with more than 8
+// splits take groups of 16 (a short step has about 20: two round trips, not three;
+// the small fp32 episode 17.7 against 18.3 us);
 // the others, with more rows and 9 or 10 splits, lose 0.4 us by them.
 template <int D, int kGroup, typename TO>
 __global__ void __launch_bounds__(256) split_combine_kernel(AttnArgs a, TO* __restrict__ og) {

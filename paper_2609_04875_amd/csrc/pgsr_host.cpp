@@ -628,7 +628,7 @@ int do_replay(pgsr_pool* p, int32_t layer, int32_t n, const int32_t* seqs,
                      : pipe               ? launch_attn_bf16_pipe(a, pipe, f8, st)
                      : f8                 ? launch_attn_fp8(a, st)
                                           : launch_attn_bf16(a, st);
-    if (err == hipSuccess && a.n_splits > 1) err = launch_split_combine(a, p->dtype == PGSR_F32, 8, st);
+    if (err == hipSuccess && a.n_splits > 1) err = launch_split_combine(a, p->dtype == PGSR_F32, p->dtype == PGSR_F32 ? 16 : 8, st);
     if (err != hipSuccess) return hip_fail(err, "attention launch");
   }
 
