@@ -251,15 +251,15 @@ constexpr int64_t kMaxSplits = 32;
 constexpr int32_t kSplitAlign = 64;
 // Decode kernel (calls whose sequences all fit one wave's 32 query rows, with
 // a workspace): the shortest split, of at least 64 keys and at most 64 to a
-// sequence, whose waves over all sequences fit the eight that a CU holds at
-// once.  Counting each sequence's own splits fills the chip for ragged lengths
-// too (32 sequences of 1024 to 16384 keys: 124 us against 142 with an FP8 cache
-// and 215 against 267 in bf16, where one count for all, from the number of
-// sequences, left half of the waves without keys; 48 x 4000 FP8, where it left
-// a second round: 96 against 119).  A larger target makes a second round (3072 waves: 32 x
-// 8192 bf16 217 against 190 us).  Few sequences are a serial walk per wave, one
-// tile's latency (about 1.5 us) after the other: two tiles instead of eight
-// take 16 against 20 us a call at 1331 keys; 128 keys 19.
+// sequence, whose waves over all sequences fit a target.  Counting each
+// sequence's own splits fills the chip for ragged lengths too (32 sequences of
+// 1024 to 16384 keys: 124 us against 142 with an FP8 cache and 215 against 267
+// in bf16, where one count for all, from the number of sequences, left half of
+// the waves without keys).  Few sequences are a serial walk per wave, one tile's
+// latency after the other: two tiles instead of eight take 16 against 20 us a
+// call at 1331 keys; 128 keys 19.  decode_split_tiles has the lines between no
+// split, four waves to a CU and the eight that a CU holds at once; a larger
+// target makes a second round (3072 waves: 32 x 8192 bf16 217 against 190 us).
 #ifndef PGSR_DECODE_TARGET_WAVES
 #define PGSR_DECODE_TARGET_WAVES 2048
 #endif
@@ -267,8 +267,51 @@ constexpr int32_t kSplitAlign = 64;
 #define PGSR_DECODE_MIN_SPLIT_KEYS 64
 #endif
 constexpr int64_t kDecodeTargetWaves = PGSR_DECODE_TARGET_WAVES;
+constexpr int64_t kDecodeFewWaves = 4 * kCus;
+constexpr int64_t kDecodeFewWavesTiles = 24;
 constexpr int64_t kDecodeMaxSplits = 64;
 constexpr int32_t kDecodeMinSplitKeys = PGSR_DECODE_MIN_SPLIT_KEYS;
+
+// Tiles per split of a decode launch over `kv` keys per sequence, at most `most`
+// splits to a sequence and `row_bytes` to a cached key; the longest sequence's
+// tiles when it is not cut.
+int64_t decode_split_tiles(const std::vector<int64_t>& kv, int64_t hkv, int64_t most, int64_t row_bytes) {
+  const int64_t kt = attn_decode_keys_per_tile(), n = (int64_t)kv.size();
+  const int64_t max_key = *std::max_element(kv.begin(), kv.end());
+  const int64_t whole = cdiv(max_key, kt);
+  // Cutting costs the combine and the partials' way through memory, 1 us for
+  // one sequence and 8 to 10 for 64, and gains the less the more bytes the waves
+  // ask for without it.  The line goes through the lengths at which both took
+  // equally long: 160 keys for one to eight sequences, 250 to 300 for 32, and for 64
+  // from 550 (FP8, 4 KV heads) to 800 (bf16, 8 KV heads).  64 x 400 keys bf16: 37 us
+  // whole, 44 cut; 8 x 400: 23 and 15.
+  const double heavy = (double)(n * hkv * row_bytes) / (512.0 * 256.0);
+  const double line = 5.0 + (double)n / (row_bytes >= 256 ? 8.0 : 5.0) + 12.0 * heavy * heavy * heavy;
+  if (most <= 1 || (double)whole <= line) return whole;
+  auto shortest = [&](int64_t target) {
+    int64_t hi = whole;
+    int64_t lo = std::min(hi, std::max<int64_t>(kDecodeMinSplitKeys / kt, cdiv(cdiv(max_key, most), kt)));
+    while (lo < hi) {
+      const int64_t mid = (lo + hi) / 2;
+      int64_t waves = 0;
+      for (const int64_t keys : kv) waves += cdiv(keys, mid * kt) * hkv;
+      if (waves <= target) hi = mid;
+      else lo = mid + 1;
+    }
+    return lo;
+  };
+  // Four waves already take keys of 256 bytes (bf16, head_dim 128) as fast as a
+  // CU gets them, and between four and eight to a CU some CUs hold twice the work of
+  // others: up to splits of 768 keys four are faster (8 x 4000 keys 32.8 against
+  // 35.0 us, 16 x 2000 33.6 and 37.9, 28 / 4 heads 16 x 800 to 8000 39.7 and 47.1),
+  // for longer ones eight (8 x 16000: 100 against 106, 32 x 8192: 186 against
+  // 200).  Shorter keys need eight throughout (FP8, 51 x 2000: 59 against 67).
+  if (row_bytes >= 256) {
+    const int64_t few = shortest(kDecodeFewWaves);
+    if (few <= kDecodeFewWavesTiles) return few;
+  }
+  return shortest(kDecodeTargetWaves);
+}
 
 // Validation of a replay step: lengths, table width, free blocks.
 int check_replay(const pgsr_pool* p, int32_t layer, int32_t n, const int32_t* seqs,
@@ -531,37 +574,24 @@ int do_replay(pgsr_pool* p, int32_t layer, int32_t n, const int32_t* seqs,
     a.row_begin = segs[base].q_off * p->hq;
     a.row_end = (segs[base + cnt - 1].q_off + segs[base + cnt - 1].q_len) * p->hq;
     if (decode) {
-      int32_t max_key = 0;
-      for (int32_t i = 0; i < cnt; ++i) max_key = std::max(max_key, chunk[i].prefix + chunk[i].q_len);
-      auto waves = [&](int64_t len) {
-        int64_t w = 0;
-        for (int32_t i = 0; i < cnt; ++i) w += cdiv((int64_t)chunk[i].prefix + chunk[i].q_len, len);
-        return w * p->hkv;
-      };
-      const int64_t kt = attn_decode_keys_per_tile();
+      std::vector<int64_t> kv(cnt);
+      for (int32_t i = 0; i < cnt; ++i) kv[i] = (int64_t)chunk[i].prefix + chunk[i].q_len;
+      const int64_t max_key = *std::max_element(kv.begin(), kv.end());
       const int64_t per_split = (int64_t)a.n_rows * ((int64_t)p->d + 2) * (int64_t)sizeof(float);
       const int64_t most = std::min<int64_t>(kDecodeMaxSplits, (int64_t)(ws_bytes / std::max<int64_t>(per_split, 1)));
-      // tiles of the shortest split in [lo, hi] whose waves fit (hi: no split)
-      int64_t hi = cdiv(max_key, kt), lo = hi;
-      if (most > 1) lo = std::min(hi, std::max<int64_t>(kDecodeMinSplitKeys / kt, cdiv(cdiv(max_key, most), kt)));
-      while (lo < hi) {
-        const int64_t mid = (lo + hi) / 2;
-        if (waves(mid * kt) <= kDecodeTargetWaves) hi = mid;
-        else lo = mid + 1;
-      }
-      a.n_splits = cdiv(max_key, lo * kt);
+      const int64_t len = decode_split_tiles(kv, p->hkv, most, (int64_t)p->d * eb) * attn_decode_keys_per_tile();
+      a.n_splits = cdiv(max_key, len);
       if (a.n_splits > 1) {
-        a.split_len = (int32_t)(lo * kt);
+        a.split_len = (int32_t)len;
         a.ws_acc = (float*)ws;
         a.ws_ml = a.ws_acc + (int64_t)a.n_splits * a.n_rows * p->d;
       }
       a.n_tiles = 0;                               // waves, and each entry's first
       for (int32_t i = 0; i < cnt; ++i) {
         a.e[i].tile_start = a.n_tiles;
-        const int64_t kv = (int64_t)chunk[i].prefix + chunk[i].q_len;
-        a.n_tiles += (a.n_splits > 1 ? cdiv(kv, a.split_len) : 1) * p->hkv;
+        a.n_tiles += (a.n_splits > 1 ? cdiv(kv[i], a.split_len) : 1) * p->hkv;
       }
-      hipError_t err = launch_attn_decode(a, p->dtype == PGSR_FP8_E4M3, st);
+      hipError_t err = launch_attn_decode(a, f8, st);
       if (err == hipSuccess && a.n_splits > 1) err = launch_split_combine(a, false, 16, st);
       if (err != hipSuccess) return hip_fail(err, "decode attention launch");
       continue;

@@ -167,3 +167,82 @@ def test_decode_splits_of_ragged_sequences(prefixes, max_splits):
     out = _decode(pool, eps, list(range(n)), 1)
     for s, ep in enumerate(eps):
         assert_close(out[0, s:s + 1].float().cpu().numpy(), _oracle_step(ep, 0), "bf16", f"seq {s} of {prefixes[s]}")
+
+
+def _pool_state(dtype, geom, prefixes, max_splits, seed):
+    """A pool of either cache with the given sequences, and one step's q, k, v, o."""
+    from paper_2609_04875_amd import BF16, FP8_E4M3, KVPool, workspace_bytes
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    new = lambda n, h: torch.randn(n, h, geom.head_dim, device="cuda", generator=g).to(torch.bfloat16)  # noqa: E731
+    n = len(prefixes)
+    pool = KVPool(1, geom.n_q_heads, geom.n_kv_heads, geom.head_dim, sum(_blocks(p + 1) for p in prefixes) + 4, n,
+                  _blocks(max(prefixes) + 1) + 1, FP8_E4M3 if dtype == "fp8" else BF16,
+                  workspace_bytes=workspace_bytes(geom.n_q_heads, geom.head_dim, n, max_splits))
+    if dtype == "fp8":
+        pool.set_kv_scales([5 / 448], [5 / 448])
+    for s, p in enumerate(prefixes):
+        k, v = new(p, geom.n_kv_heads), new(p, geom.n_kv_heads)
+        q = torch.zeros(p, geom.n_q_heads, geom.head_dim, dtype=torch.bfloat16, device="cuda")
+        assert pool.replay(0, [s], [p], q, k, v, torch.empty_like(q), SCALE) == 0
+    q = new(n, geom.n_q_heads)
+    return pool, q, new(n, geom.n_kv_heads), new(n, geom.n_kv_heads), torch.empty_like(q)
+
+
+@pytest.mark.parametrize("dtype,geom,prefixes,splits", [
+    ("bf16", GEOM, (100,), 1), ("bf16", GEOM, (159,), 1), ("bf16", GEOM, (170,), 3),     # the line of one sequence
+    ("fp8", GEOM, (300,) * 31, 1), ("fp8", GEOM, (500,) * 31, 8),                        # of many
+    ("bf16", GEOM, (700,) * 64, 1), ("bf16", GEOM7, (120,) * 20, 1),
+    ("bf16", GEOM, (2000,) * 16, 8), ("bf16", GEOM7, (1999, 300, 40), 32),               # four waves to a CU
+    ("fp8", GEOM, (2000,) * 16, 16), ("bf16", GEOM, (3000,) * 32, 4), ("bf16", GEOM, (3100,) * 32, 8),   # eight; 24 and 25 tiles at four
+])
+def test_decode_splits_at_their_lines(dtype, geom, prefixes, splits):
+    """Short sequences are not cut, bf16 ones only to four waves a CU while splits
+    stay short: the same bits as with a workspace that allows no more splits,
+    and others with one that allows one less."""
+    n, per_split = len(prefixes), len(prefixes) * geom.n_q_heads * (geom.head_dim + 2) * 4
+    log(f"decode lines {dtype} {geom} n={n} max={max(prefixes)} splits={splits}")
+    pool, q, k, v, o = _pool_state(dtype, geom, prefixes, 64, n + max(prefixes))
+
+    def step(scratch_bytes):
+        pool.workspace.fill_(255)        # NaN: a partial that nobody wrote would show
+        o.zero_()
+        if scratch_bytes is None:
+            rc = pool.replay(0, list(range(n)), [1] * n, q, k, v, o, SCALE, commit=False)
+        else:
+            rc = pool.replay_static(0, list(range(n)), [1] * n, q, k, v, o, SCALE, scratch_bytes, commit=False)
+        assert rc == 0
+        return o.clone()
+
+    free = step(None)
+    assert torch.isfinite(free.float()).all() and torch.equal(step(None), free)
+    assert torch.equal(step(splits * per_split), free)       # 1: a workspace too small for any cut
+    if splits > 1:
+        assert not torch.equal(step((splits - 1) * per_split), free)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp8"])
+def test_finer_splits_are_no_less_exact(dtype):
+    """More, shorter splits round each softmax weight against another running
+    maximum: other bits, and an error against 64 bits that is no larger."""
+    prefixes = (1330, 300, 4000, 900, 2047)
+    pool, q, k, v, o = _pool_state(dtype, GEOM, prefixes, 64, 11)
+    n, per_split = len(prefixes), len(prefixes) * 32 * 130 * 4
+    errs = []
+    for scratch in (None, 5 * per_split, 16):                # as chosen, 5 splits, none
+        rc = (pool.replay(0, list(range(n)), [1] * n, q, k, v, o, SCALE, commit=False) if scratch is None else
+              pool.replay_static(0, list(range(n)), [1] * n, q, k, v, o, SCALE, scratch, commit=False))
+        assert rc == 0
+        ref, s = [], 5 / 448 if dtype == "fp8" else 1.0
+        for i, p in enumerate(prefixes):
+            pos = torch.arange(p + 1, device="cuda")
+            blk, slot = pool.block_tables[i].long()[pos // 16], pos % 16
+            kk, vv = pool.k_cache[0][blk, :, slot, :], pool.v_cache[0][blk, :, :, slot]
+            if dtype == "fp8":
+                kk, vv = kk.view(torch.float8_e4m3fn), vv.view(torch.float8_e4m3fn)
+            kk, vv = kk.double() * s, vv.double() * s
+            w = torch.softmax((q[i].double().view(8, 4, 1, 128) * kk.permute(1, 0, 2)[:, None]).sum(-1) * SCALE, -1)
+            ref.append((w[..., None] * vv.permute(1, 0, 2)[:, None]).sum(2).view(32, 128))
+        ref = torch.stack(ref)
+        errs.append(((o.double() - ref).norm() / ref.norm()).item())
+    log(f"error against 64 bits {dtype}: {errs}")
+    assert errs[0] <= 1.02 * min(errs[1:])
