@@ -281,15 +281,18 @@ __device__ inline void copy_block_head(const uint16_t* __restrict__ kin, const u
 // loads of a round ahead of its stores, V back in runs of 4 (fp32) or 8 slots;
 // others element by element, and so do codes where the chunks would leave
 // threads idle (a division and the rounding per element, not the accesses, are
-// what a code costs; hence four waves).  With the crop in the same launch: 640
-// fp32 tokens restored and 128 replayed 20.7 -> 17.6 us a call, 2048 FP8 tokens
-// on 8189 about 5 of 300 us.
+// what a code costs; hence four waves).  Codes take one chunk a round: with two a
+// wave holds 103 registers instead of 83, a CU four workgroups instead of five,
+// and the short copies of a decode step wait for a second round (48 tokens x 32
+// heads 16.2 against 14.7 us; 32000 tokens x 8 heads 93 against 81).  With the
+// crop in the same launch: 640 fp32 tokens restored and 128 replayed 20.7 -> 17.6 us
+// a call, 2048 FP8 tokens on 8189 about 5 of 300 us.
 template <typename TI, typename T, int B, int D>
 __device__ inline void copy_span(const TI* __restrict__ kin, const TI* __restrict__ vin, int64_t row_stride,
                                  T* __restrict__ kc, T* __restrict__ vc, int s0, int nt, float k_scale,
                                  float v_scale, T* vstage) {
   constexpr int E = 16 / sizeof(TI), C = D / E, R = sizeof(T) == 4 ? 4 : 8;
-  constexpr int DP = D + kStagePad<T>, NT = kAppendThreads<TI, T>, J = NT == 64 ? 4 : 2;
+  constexpr int DP = D + kStagePad<T>, NT = kAppendThreads<TI, T>, J = NT == 64 ? 4 : 1;
   typedef TI in_t __attribute__((ext_vector_type(E)));
   typedef T chunk_t __attribute__((ext_vector_type(E)));
   typedef T run_t __attribute__((ext_vector_type(R)));
