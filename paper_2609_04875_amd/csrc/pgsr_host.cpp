@@ -625,11 +625,33 @@ int do_replay(pgsr_pool* p, int32_t layer, int32_t n, const int32_t* seqs,
     // FP8, 1024 tokens: pipelined with four waves 178, four-wave 209, pipelined
     // with eight 236; 2048 tokens: 346, 316 and 297.  Pools that the wide kernel
     // does not take (32- and 64-token blocks): four-wave, then pipelined.
+    auto fits = [&](int tokens) { return count_tiles(tokens) * p->hkv * a.n_splits <= kCus; };
+    // Past that the kernels with tiles of eight row blocks, one workgroup to a CU,
+    // have the cheaper step, but a tile costs them two 64-key steps more, and
+    // tiles that the sequences fill badly cost twice: with few keys or tokens to a
+    // sequence the four-wave kernel is the faster one (us a call, four-wave and the
+    // other; wide: 24 / 8 heads, 64 x 12 tokens on 100 keys 42.5, 54.7; 28 / 4
+    // heads, 8 x 312 on 43 38.9, 46.2, 4 x 509 on 832 60.0, 52.6; FP8, pipelined:
+    // 16 / 16 heads, 64 x 12 on 100 51.5, 72.8; 20 / 4, 65 x 116 on 496 90, 113).
+    // With these costs the faster one of 133 batches of 1 to 77 sequences was taken
+    // but for 0.4% of the time (always the other kernel: 6 to 11%).
+    auto steps = [&](int tokens, double per_tile, double per_step) {
+      double w = 0;
+      for (int32_t i = 0; i < cnt; ++i) {
+        const double n = cdiv(chunk[i].q_len, tokens);
+        const double keys = n * chunk[i].prefix + tokens * n * (n - 1) / 2 + chunk[i].q_len;
+        w += n * per_tile + per_step * (keys / 64 + n / 2);
+      }
+      return w;
+    };
+    auto eight_pays = [&](double per_tile, double per_step) {
+      return 2 * steps(attn_bf16_pipe_tile_tokens(group, 8), per_tile, per_step) <
+             steps(attn_bf16_tile_tokens(p->d, group), 3, 1);
+    };
     // Split bf16 calls with groups that do not divide 32 were cut for the
     // four-wave kernel, two workgroups to a CU, and keep it (28 / 4 heads, 3 x
     // 126 tokens on 1600: 38.7 us, wide 50.7; 400 tokens on 900, narrow 35.4
     // against 31.2).
-    auto fits = [&](int tokens) { return count_tiles(tokens) * p->hkv * a.n_splits <= kCus; };
     int narrow = 0, pipe = 0;       // waves per workgroup of the kernel taken
     bool wide = false;
     if (p->dtype == PGSR_F32) {
@@ -638,13 +660,17 @@ int do_replay(pgsr_pool* p, int32_t layer, int32_t n, const int32_t* seqs,
       narrow = fits(attn_bf16_narrow_tile_tokens(group, 2))   ? 2
                : fits(attn_bf16_narrow_tile_tokens(group, 4)) ? 4
                                                               : 0;
-      wide = narrow == 0;
-      set_tiles(wide ? attn_bf16_pipe_tile_tokens(group, 8) : attn_bf16_narrow_tile_tokens(group, narrow));
+      wide = narrow == 0 && (32 % group == 0 || eight_pays(5, 0.75));
     } else if (pipe_ok && (f8 || split_as_wide || a.n_splits == 1)) {
-      const bool few = p->prefill_kind == PGSR_PREFILL_AUTO && fits(attn_bf16_pipe_tile_tokens(group, 4));
-      pipe = !few ? 8 : f8 ? 4 : 0;
-      set_tiles(pipe ? attn_bf16_pipe_tile_tokens(group, pipe) : attn_bf16_tile_tokens(p->d, group));
+      if (p->prefill_kind == PGSR_PREFILL_PIPELINED) pipe = 8;
+      else if (fits(attn_bf16_pipe_tile_tokens(group, 4))) pipe = f8 ? 4 : 0;
+      else if (a.n_splits > 1) pipe = 8;
+      else pipe = (!f8 && 32 % group == 0) || eight_pays(f8 ? 5 : 4, f8 ? 0.8 : 0.85) ? 8 : 0;
     }
+    if (p->dtype != PGSR_F32)
+      set_tiles(narrow         ? attn_bf16_narrow_tile_tokens(group, narrow)
+                : wide || pipe ? attn_bf16_pipe_tile_tokens(group, wide ? 8 : pipe)
+                               : attn_bf16_tile_tokens(p->d, group));
     if (p->timing && p->clk && (narrow || wide || pipe)) {
       hipError_t err = hipMemsetAsync(p->clk, 0, (size_t)p->clk_n * 4 * sizeof(uint64_t), st);
       if (err != hipSuccess) return hip_fail(err, "clock probe reset");

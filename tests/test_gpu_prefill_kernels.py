@@ -223,3 +223,64 @@ def test_default_kernel_equals_four_wave_at_its_lines(hq, hkv, B, ps, ws_tokens)
             assert_close(got.float().cpu().numpy(), oracle_suffix(e, scale, rows=rows), "bf16",
                          f"P={e.prefix} S={e.suffix}")
         off += e.suffix
+
+
+def _workgroups(pool, call, at_most=1 << 15):
+    """Workgroups of the call's prefill launch that wrote the clock probe (the
+    four-wave kernel has none): with the grid of each kernel's tiles, which one ran."""
+    pool.set_clock_probe(at_most)
+    pool.enable_timing(True)
+    call()
+    torch.cuda.synchronize()
+    pool.enable_timing(False)
+    return int((pool._clk.view(-1, 4)[:, 1] != 0).sum())
+
+
+# (dtype, Hq, Hkv, B, [(P, S), ...], kernel the call runs, waves that own 32 query rows each to a workgroup)
+TAKEN = [
+    # tiles of eight row blocks that short or few-token sequences fill badly: the four-wave kernel
+    ("fp8", 16, 16, 16, [(100, 12)] * 64, "four-wave", 0),
+    ("fp8", 20, 4, 32, [(400, 116)] * 50, "four-wave", 0),
+    ("bf16", 24, 8, 16, [(100, 12)] * 64, "four-wave", 0),
+    ("bf16", 28, 4, 64, [(90, 45)] * 33, "four-wave", 0),
+    ("bf16", 28, 4, 16, [(43, 312)] * 8, "four-wave", 0),          # 5 key tiles to a query tile
+    ("bf16", 28, 4, 16, [(832, 509)] * 4, "wide", 8),              # 17
+    ("bf16", 28, 4, 32, [(900, 700)] * 3, "pipelined", 8),
+    ("fp8", 32, 8, 16, [(1500, 600), (900, 1000)], "pipelined", 8),
+]
+
+
+@pytest.mark.parametrize("dtype,hq,hkv,B,ps,kernel,waves", TAKEN)
+def test_kernel_taken_by_default(dtype, hq, hkv, B, ps, kernel, waves):
+    """Which kernel a call takes, its bits against the four-wave kernel's, and
+    sampled rows of two episodes against the oracle (bf16)."""
+    from paper_2609_04875_amd import BF16, FP8_E4M3, KVPool
+    geom = W.AttnGeometry(hq, hkv, 128)
+    log(f"kernel taken {dtype} {hq}/{hkv} B={B} {len(ps)} x {ps[0]}: {kernel}")
+    rng = np.random.default_rng(hq + 7 * hkv + B + len(ps))
+    eps = [W.draw_episode(rng, geom, "bf16", P, S, P + S + 3) for P, S in ps[:4]]
+    eps = [eps[i % len(eps)] for i in range(len(ps))]
+    scale = 128 ** -0.5
+    need = [_blocks(e.t_contaminated, B) + 1 for e in eps]
+    q, k, v = (torch.cat([dev(getattr(e, x)[e.prefix:], "bf16") for e in eps]) for x in ("q", "k", "v"))
+    outs = []
+    for kind in ("auto", "four_wave"):
+        pool = KVPool(1, hq, hkv, 128, sum(need) + 4, len(eps), max(need) + 2, FP8_E4M3 if dtype == "fp8" else BF16, B)
+        if dtype == "fp8":
+            pool.set_kv_scales([5 / 448], [4 / 448])
+        for i, e in enumerate(eps):
+            contaminated_then_crop(pool, e, i, scale, poison=True)
+        pool.set_prefill_kernel(kind)
+        o = torch.empty_like(q)
+        n = _workgroups(pool, lambda: pool.replay(0, list(range(len(eps))), [e.suffix for e in eps], q, k, v, o, scale))
+        tile = (waves if kind == "auto" else 0) * (32 // (hq // hkv))
+        assert n == (sum(-(-S // tile) for _, S in ps) * hkv if tile else 0), f"{kind}: {n} workgroups"
+        outs.append(o)
+    assert torch.isfinite(outs[0].float()).all() and torch.equal(outs[0], outs[1])
+    off = 0
+    for e in eps[:2]:
+        if dtype == "bf16":
+            rows = np.unique(np.concatenate([np.arange(0, e.suffix * hq, 97), np.arange(e.suffix * hq - hq, e.suffix * hq)]))
+            got = outs[0][off:off + e.suffix].reshape(-1, 128)[torch.from_numpy(rows).cuda()]
+            assert_close(got.float().cpu().numpy(), oracle_suffix(e, scale, rows=rows), "bf16", f"P={e.prefix} S={e.suffix}")
+        off += e.suffix
