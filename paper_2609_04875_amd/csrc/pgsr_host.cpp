@@ -648,10 +648,11 @@ int do_replay(pgsr_pool* p, int32_t layer, int32_t n, const int32_t* seqs,
       return 2 * steps(attn_bf16_pipe_tile_tokens(group, 8), per_tile, per_step) <
              steps(attn_bf16_tile_tokens(p->d, group), 3, 1);
     };
-    // Split bf16 calls with groups that do not divide 32 were cut for the
+    // Split calls of FP8 pools and of groups that do not divide 32 were cut for the
     // four-wave kernel, two workgroups to a CU, and keep it (28 / 4 heads, 3 x
     // 126 tokens on 1600: 38.7 us, wide 50.7; 400 tokens on 900, narrow 35.4
-    // against 31.2).
+    // against 31.2; FP8, 32 / 16 heads, 300 tokens on 2000 45, pipelined 51) but for
+    // FP8 calls whose larger tiles all have a CU (450 tokens: 51, pipelined 44).
     int narrow = 0, pipe = 0;       // waves per workgroup of the kernel taken
     bool wide = false;
     if (p->dtype == PGSR_F32) {
@@ -664,7 +665,7 @@ int do_replay(pgsr_pool* p, int32_t layer, int32_t n, const int32_t* seqs,
     } else if (pipe_ok && (f8 || split_as_wide || a.n_splits == 1)) {
       if (p->prefill_kind == PGSR_PREFILL_PIPELINED) pipe = 8;
       else if (fits(attn_bf16_pipe_tile_tokens(group, 4))) pipe = f8 ? 4 : 0;
-      else if (a.n_splits > 1) pipe = 8;
+      else if (a.n_splits > 1) pipe = !f8 || fits(attn_bf16_pipe_tile_tokens(group, 8)) ? 8 : 0;
       else pipe = (!f8 && 32 % group == 0) || eight_pays(f8 ? 5 : 4, f8 ? 0.8 : 0.85) ? 8 : 0;
     }
     if (p->dtype != PGSR_F32)

@@ -93,3 +93,14 @@ def oracle_suffix(ep: W.Episode, scale: float, rows=None) -> np.ndarray:
     k = storage_f64(ep.k, ep.dtype)
     v = storage_f64(ep.v, ep.dtype)
     return oracle.attention(q, k, v, ep.prefix, scale, rows=rows)
+
+
+def probed_workgroups(pool, call, at_most=1 << 15):
+    """Workgroups of the call's prefill launch that wrote the clock probe (the
+    four-wave kernel has none): with the grid of each kernel's tiles, which one ran."""
+    pool.set_clock_probe(at_most)
+    pool.enable_timing(True)
+    call()
+    torch.cuda.synchronize()
+    pool.enable_timing(False)
+    return int((pool._clk.view(-1, 4)[:, 1] != 0).sum())

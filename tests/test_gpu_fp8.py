@@ -10,7 +10,7 @@ import torch
 
 import oracle
 import workloads as W
-from gpu_helpers import assert_close, dev, log, storage_f64
+from gpu_helpers import assert_close, dev, log, probed_workgroups, storage_f64
 
 pytestmark = pytest.mark.gpu
 
@@ -300,3 +300,56 @@ def test_fp8_default_prefill_kernel_equals_four_wave(hq, hkv, B, ps):
         assert torch.isfinite(o.float()).all()
         outs.append(o)
     assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+
+
+@pytest.mark.parametrize("hq,hkv,B,ps,split_len,tile_waves", [
+    (32, 8, 16, [(100, 60)], 64, 4),                       # pipelined, four waves: 2 tiles x 8 heads x 3 splits
+    (28, 4, 32, [(600, 100)], 64, 8),                      # eight waves, padded rows
+    (32, 8, 16, [(2000, 500)], 640, 8),                    # 8 tiles x 8 heads x 4 = 256
+    (32, 16, 64, [(2000, 450)], 640, 8),
+    (32, 8, 16, [(2000, 400)], 512, 0),                    # 280 of the larger tiles: four-wave
+    (32, 16, 16, [(2000, 300)], 384, 0), (28, 4, 16, [(700, 100), (90, 40)], 64, 0)])
+def test_fp8_split_prefill(hq, hkv, B, ps, split_len, tile_waves):
+    """A call with a workspace is cut into splits for the four-wave kernel's tiles;
+    the pipelined kernel takes it where its larger tiles all have a CU.  The same
+    bits from all three, over poisoned tails, against attention in 64 bits over
+    the codes that the cache holds."""
+    geom, scale, ks, vs = W.AttnGeometry(hq, hkv, 128), 128 ** -0.5, 5 / 448, 4 / 448
+    log(f"fp8 split prefill {hq}/{hkv} B={B} {ps}")
+    rng = np.random.default_rng(hq + B + sum(p for p, _ in ps))
+    eps = [W.draw_episode(rng, geom, "bf16", P, S, P + S + 3) for P, S in ps]
+    total = sum(S for _, S in ps)
+    q, k, v = (torch.cat([dev(getattr(e, x)[e.prefix:], "bf16") for e in eps]) for x in ("q", "k", "v"))
+    outs = []
+    for kind in ("auto", "pipelined", "four_wave"):
+        nb = sum(-(-(P + S + 3) // B) for P, S in ps)
+        pool = _pool(geom, 1, 2 * nb + 4, len(ps), nb + 2, B, split_q=total)
+        pool.set_kv_scales([ks], [vs])
+        for i, e in enumerate(eps):
+            cq, ck, cv = (dev(e.contaminated(x), "bf16") for x in ("q", "k", "v"))
+            assert pool.replay(0, [i], [e.t_contaminated], cq, ck, cv, torch.empty_like(cq), scale) == 0
+        assert pool.crop(list(range(len(ps))), [e.prefix for e in eps], poison=True) == 0
+        pool.set_prefill_kernel(kind)
+        pool.workspace.fill_(255)
+        o = torch.empty_like(q)
+        n = probed_workgroups(pool, lambda: pool.replay(0, list(range(len(ps))), [S for _, S in ps], q, k, v, o, scale))
+        waves = {"auto": tile_waves, "pipelined": 8, "four_wave": 0}[kind]
+        # a workgroup whose split starts past its tile's last key leaves before the probe
+        tile = waves * (32 // (hq // hkv))
+        want = hkv * sum(-(-(P + min(S, t0 + tile)) // split_len) for P, S in ps for t0 in range(0, S, tile)) if tile else 0
+        assert n == want, f"{kind}: {n} workgroups, not {want}"
+        outs.append(o)
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+    off = 0
+    for i, (P, S) in enumerate(ps):
+        pos = torch.arange(P + S, device="cuda")
+        blk, slot = pool.block_tables[i].long()[pos // B], pos % B
+        kk = pool.k_cache[0][blk, :, slot, :].view(torch.float8_e4m3fn).double() * ks
+        vv = pool.v_cache[0][blk, :, :, slot].view(torch.float8_e4m3fn).double() * vs
+        for h in (0, hq - 1):
+            g = h // (hq // hkv)
+            w = (q[off:off + S, h].double()[:, None] * kk[None, :, g]).sum(-1) * scale
+            w = torch.softmax(w.masked_fill(pos[None] > P + torch.arange(S, device="cuda")[:, None], -np.inf), -1)
+            ref = (w[..., None] * vv[None, :, g]).sum(1)
+            assert_close(outs[0][off:off + S, h].float().cpu().numpy(), ref.cpu().numpy(), "bf16", f"seq {i} head {h}")
+        off += S

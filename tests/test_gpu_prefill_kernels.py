@@ -14,7 +14,7 @@ import pytest
 import torch
 
 import workloads as W
-from gpu_helpers import assert_close, contaminated_then_crop, dev, log, make_pool, oracle_suffix
+from gpu_helpers import assert_close, contaminated_then_crop, dev, log, make_pool, oracle_suffix, probed_workgroups
 
 pytestmark = pytest.mark.gpu
 
@@ -225,17 +225,6 @@ def test_default_kernel_equals_four_wave_at_its_lines(hq, hkv, B, ps, ws_tokens)
         off += e.suffix
 
 
-def _workgroups(pool, call, at_most=1 << 15):
-    """Workgroups of the call's prefill launch that wrote the clock probe (the
-    four-wave kernel has none): with the grid of each kernel's tiles, which one ran."""
-    pool.set_clock_probe(at_most)
-    pool.enable_timing(True)
-    call()
-    torch.cuda.synchronize()
-    pool.enable_timing(False)
-    return int((pool._clk.view(-1, 4)[:, 1] != 0).sum())
-
-
 # (dtype, Hq, Hkv, B, [(P, S), ...], kernel the call runs, waves that own 32 query rows each to a workgroup)
 TAKEN = [
     # tiles of eight row blocks that short or few-token sequences fill badly: the four-wave kernel
@@ -272,7 +261,7 @@ def test_kernel_taken_by_default(dtype, hq, hkv, B, ps, kernel, waves):
             contaminated_then_crop(pool, e, i, scale, poison=True)
         pool.set_prefill_kernel(kind)
         o = torch.empty_like(q)
-        n = _workgroups(pool, lambda: pool.replay(0, list(range(len(eps))), [e.suffix for e in eps], q, k, v, o, scale))
+        n = probed_workgroups(pool, lambda: pool.replay(0, list(range(len(eps))), [e.suffix for e in eps], q, k, v, o, scale))
         tile = (waves if kind == "auto" else 0) * (32 // (hq // hkv))
         assert n == (sum(-(-S // tile) for _, S in ps) * hkv if tile else 0), f"{kind}: {n} workgroups"
         outs.append(o)
