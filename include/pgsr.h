@@ -290,18 +290,31 @@ int pgsr_pool_last_clock(pgsr_pool *pool, void *stream, double *ghz, int64_t *cy
 
 /*
  * Choice of the prefill attention kernel of bf16 and FP8 pools (Algorithm 1
- * replay loop, prefill form) for head_dim 128.  PGSR_PREFILL_AUTO (the
- * default) runs, for a bf16 pool with 16-token blocks, n_blocks * n_kv_heads *
- * 4 KB <= 4 GB and no sequence of the call past 130816 keys (prefix + suffix),
- * the wide kernel (one wave per SIMD, 64 query rows per wave, global->LDS tile
- * loads) or, for calls that leave CUs idle, the narrow one (32 query rows per
- * wave); for other bf16 pools and FP8 pools the software-pipelined kernel
- * (32 query rows per wave, two waves per SIMD, FP8 calls that leave CUs idle
- * one) or, for bf16 calls that leave CUs idle, the four-wave kernel.
- * PGSR_PREFILL_PIPELINED always runs the pipelined kernel with two waves per
- * SIMD; PGSR_PREFILL_FOUR_WAVE the four-wave kernel, as head_dim 64 does.  All
- * give identical bits for every query row; the option only moves time.  Host
- * only, no device work; EINVAL for another value.
+ * replay loop, prefill form) for head_dim 128; head_dim 64 always runs the
+ * four-wave kernel, and with a workspace calls of at most 32 / G query tokens to a
+ * sequence the decode kernel.
+ *
+ * PGSR_PREFILL_AUTO (the default), by the cache, the block size and the call:
+ *  - bf16, 16-token blocks, n_blocks * n_kv_heads * 4 KB <= 4 GB and no sequence
+ *    of the call past 130816 keys (prefix + suffix): the wide kernel (one wave per
+ *    SIMD, 64 query rows per wave, global->LDS tile loads) or, for calls that
+ *    leave CUs idle, the narrow one (32 query rows per wave);
+ *  - other bf16 pools and FP8 pools: the software-pipelined kernel (32 query rows
+ *    per wave, two waves per SIMD) or, for calls that leave CUs idle, with one
+ *    wave per SIMD (FP8) or the four-wave kernel (bf16);
+ *  - the four-wave kernel for batches whose sequences fill the larger tiles badly
+ *    (FP8, and groups G = n_q_heads / n_kv_heads that do not divide 32), for
+ *    calls with split keys of such groups in bf16, and for those of FP8 pools whose
+ *    larger tiles do not all have a CU.
+ * PGSR_PREFILL_PIPELINED runs the pipelined kernel with two waves per SIMD, but for
+ * bf16 calls with split keys of a group that does not divide 32, which stay with
+ * the four-wave kernel.  PGSR_PREFILL_FOUR_WAVE runs the four-wave kernel.
+ *
+ * All kernels give identical bits for every query row of calls that are not split
+ * (no workspace, or enough workgroups without).  Splits round: their number is the
+ * same under every choice for FP8 pools and for groups that do not divide 32, and
+ * under AUTO and PIPELINED for the others, where FOUR_WAVE cuts for its own tiles.
+ * Host only, no device work; EINVAL for another value.
  */
 enum { PGSR_PREFILL_AUTO = 0, PGSR_PREFILL_FOUR_WAVE = 1, PGSR_PREFILL_PIPELINED = 2 };
 int pgsr_pool_set_prefill_kernel(pgsr_pool *pool, int kind);

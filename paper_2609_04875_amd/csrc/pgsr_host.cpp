@@ -511,8 +511,10 @@ int do_replay(pgsr_pool* p, int32_t layer, int32_t n, const int32_t* seqs,
   for (const Seg& g : segs) decode = decode && g.q_len <= 32 / group;
   int64_t max_kv = 0;
   for (const Seg& g : segs) max_kv = std::max<int64_t>(max_kv, (int64_t)g.prefix + g.q_len);
-  // Kernels of one arithmetic (the same bits for every row), so the choice only
-  // moves time; the tile they share decides how many splits a call takes.
+  // Kernels of one arithmetic (the same bits for every row of one split plan).  The
+  // plan is cut for the tiles of one of them: the four-wave kernel's where
+  // PGSR_PREFILL_FOUR_WAVE asks for it, for FP8 and for groups that do not divide
+  // 32, the larger ones of the others else.
   const bool f8 = p->dtype == PGSR_FP8_E4M3;
   const bool wide_ok = p->dtype == PGSR_BF16 && p->prefill_kind == PGSR_PREFILL_AUTO &&
                        attn_bf16_wide_eligible(p->d, group, p->B, p->n_blocks, p->hkv, max_kv);

@@ -125,7 +125,8 @@ class KVPool:
 
     def set_prefill_kernel(self, kind: str) -> None:
         """Prefill kernel of a head_dim 128 bf16 or FP8 pool: "auto" (by size,
-        cache and block size), "pipelined" or "four_wave"; the same bits."""
+        cache and block size), "pipelined" or "four_wave"; the same bits for calls
+        with the same number of splits (without a workspace always)."""
         code = {"auto": 0, "four_wave": 1, "pipelined": 2}[kind]
         N.check(N.lib.pgsr_pool_set_prefill_kernel(self._h, code))
 

@@ -202,10 +202,9 @@ def test_default_kernel_equals_four_wave_at_its_lines(hq, hkv, B, ps, ws_tokens)
         nb = sum(_blocks(e.t_contaminated, B) + _blocks(e.t_sanitized, B) for e in eps) + 4
         mbps = max(_blocks(max(e.t_contaminated, e.t_sanitized), B) for e in eps) + 2
         pool = make_pool(geom, "bf16", nb, len(eps), mbps, block_size=B, split_q=ws_tokens, max_splits=8)
-        if not ws_tokens:                # a split call's bits depend on its number of splits
-            pool.set_prefill_kernel(kind)
-        elif kind != "auto":
-            continue
+        if ws_tokens and kind == "four_wave" and 32 % (hq // hkv) == 0:
+            continue                     # cut for its own tiles: another number of splits, other bits
+        pool.set_prefill_kernel(kind)
         for i, e in enumerate(eps):
             contaminated_then_crop(pool, e, i, scale, poison=True)
         q, k, v = (torch.cat([dev(getattr(e, x)[e.prefix:], "bf16") for e in eps]) for x in ("q", "k", "v"))
@@ -213,8 +212,8 @@ def test_default_kernel_equals_four_wave_at_its_lines(hq, hkv, B, ps, ws_tokens)
         assert pool.replay(0, list(range(len(eps))), [e.suffix for e in eps], q, k, v, o, scale) == 0
         torch.cuda.synchronize()
         outs[kind] = o
-    for kind, o in outs.items():
-        assert torch.equal(o, outs["auto"]), f"{kind} differs from the default kernel"
+    for kind in set(outs) - {"auto"}:
+        assert torch.equal(outs[kind], outs["auto"]), f"{kind} differs from the default kernel"
     off = 0
     for i, e in enumerate(eps):
         if i < 2:
@@ -223,6 +222,34 @@ def test_default_kernel_equals_four_wave_at_its_lines(hq, hkv, B, ps, ws_tokens)
             assert_close(got.float().cpu().numpy(), oracle_suffix(e, scale, rows=rows), "bf16",
                          f"P={e.prefix} S={e.suffix}")
         off += e.suffix
+
+
+@pytest.mark.parametrize("hq,hkv,P,S,split_len,auto_waves,pipe_waves", [
+    (32, 8, 900, 40, 128, 2, 8),         # groups that divide 32: narrow or wide, and pipelined, one plan
+    (64, 8, 700, 300, 256, 8, 8),
+    (28, 4, 2000, 130, 320, 0, 0),       # others: the four-wave kernel under every choice
+])
+def test_split_calls_of_each_choice(hq, hkv, P, S, split_len, auto_waves, pipe_waves):
+    """Which kernel a bf16 call with split keys runs under each choice, and that
+    one plan gives one result."""
+    geom = W.AttnGeometry(hq, hkv, 128)
+    ep = W.draw_episode(np.random.default_rng(hq + P), geom, "bf16", P, S, P + S + 3)
+    q, k, v = (dev(getattr(ep, x)[P:], "bf16") for x in ("q", "k", "v"))
+    outs = {}
+    for kind, waves in (("auto", auto_waves), ("pipelined", pipe_waves), ("four_wave", 0)):
+        pool = make_pool(geom, "bf16", 2 * _blocks(P + S + 3, 16) + 4, 1, _blocks(P + S + 3, 16) + 2, split_q=S, max_splits=8)
+        contaminated_then_crop(pool, ep, 0, 128 ** -0.5, poison=True)
+        pool.set_prefill_kernel(kind)
+        o = torch.empty_like(q)
+        n = probed_workgroups(pool, lambda: pool.replay(0, [0], [S], q, k, v, o, 128 ** -0.5))
+        tile = waves * (32 // (hq // hkv))
+        # a workgroup whose split starts past its tile's last key leaves before the probe
+        want = hkv * sum(-(-(P + min(S, t + tile)) // split_len) for t in range(0, S, tile)) if tile else 0
+        assert n == want, f"{kind}: {n} workgroups, not {want}"
+        outs[kind] = o
+    assert torch.equal(outs["auto"], outs["pipelined"])
+    if 32 % (hq // hkv):                 # else the four-wave kernel cuts for its own tiles
+        assert torch.equal(outs["auto"], outs["four_wave"])
 
 
 # (dtype, Hq, Hkv, B, [(P, S), ...], kernel the call runs, waves that own 32 query rows each to a workgroup)
