@@ -151,16 +151,56 @@ __device__ inline uint64_t scan_exact(const T* lr, const SampleArgs& a, uint64_t
   return best;
 }
 
+// Where the best l / T of the chunk is at least this far from 0, fp32 values lie 64
+// apart and -log(-log u), between -2.9 and 16.7, rounds away: the scores there are
+// l / T itself, and every entry below the best keeps its distance.
+constexpr float kNoiseless = 6e8f;
+
+// Best key over this thread's entries of l / T alone, and the best of that.
+template <typename T, bool VEC>
+__device__ inline uint64_t scan_noiseless(const T* lr, const SampleArgs& a, int32_t v_lo, int32_t v_hi, float& hi) {
+  uint64_t best = 0;
+  for (int32_t v0 = v_lo + 4 * (int32_t)threadIdx.x; v0 < v_hi; v0 += 4 * kThreads) {
+    float l[4];
+    load4<T, VEC>(lr, v0, v_hi, l);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float s = l[j] / a.temperature;
+      hi = fmaxf(hi, s);                            // NaN counts as -inf
+      const uint64_t k = make_key(s, v0 + j);
+      if (v0 + j < v_hi) best = k > best ? k : best;
+    }
+  }
+  return best;
+}
+
+// Best value over the workgroup's threads (red: one slot per wave, free again after
+// the next barrier).
+__device__ inline float max_block(float x, float* red) {
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) x = fmaxf(x, __shfl_xor(x, off));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kThreads / 64; ++w) x = fmaxf(x, red[w]);
+  return x;
+}
+
 // Bound by ALU: ten Philox rounds of two 64 x 64-bit products per four
 // entries, then the scores.  Scoring every entry exactly (two logf, a division)
 // costs as much as the generator, and only the winner's score has to be exact:
 // each thread keeps its best rough score with what made it (and its second
 // best), the workgroup takes the best rough score of the chunk, and the threads
-// within twice the rough score's error of it score their candidate exactly.  A
-// thread whose second best is within it too (or a row of infinities, where no
-// margin holds) scans its entries again exactly.  32 rows x 128256 bf16 logits:
-// 21-22 -> 14.5 us with the reduction, where the calling program's own time per
-// call is as long; 64 x 151936: 39.5 -> 28.5 us.
+// within a margin of it score their candidate exactly (2e-3 and 2e-6 of the
+// score, some hundred times what the rough one can be off).  A thread whose
+// second best is within it too scans its entries again exactly.  32 rows x 128256
+// bf16 logits: 21-22 -> 14.5 us with the reduction, where the calling program's own
+// time per call is as long; 64 x 151936: 39.5 -> 28.5 us.
+// Chunks without a likely entry (a mask of -inf, of the type's lowest value or of
+// -1e9) have no margin that tells entries apart, but the noise rounds away in
+// their scores: a scan of l / T alone, unless that is not so after all (a
+// 1 / T that overflowed).  256 rows x 128256 with 50 entries left: 127 us with every
+// entry scored exactly, 135 with the rough pass before it, 94 so; dense rows 84.
 template <typename T, bool VEC>
 __global__ void __launch_bounds__(kThreads) sample_chunk_kernel(SampleArgs a, const T* __restrict__ logits,
                                                                 int32_t* __restrict__ tokens) {
@@ -196,17 +236,17 @@ __global__ void __launch_bounds__(kThreads) sample_chunk_kernel(SampleArgs a, co
         top_v = better ? v0 + j : top_v;
       }
     }
-    float m = top;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
-    if ((threadIdx.x & 63) == 0) redf[threadIdx.x >> 6] = m;
-    __syncthreads();
-#pragma unroll
-    for (int w = 0; w < kThreads / 64; ++w) m = fmaxf(m, redf[w]);
-    // NaN where the best is infinite: then no thread is below the line
-    const float line = m - (2e-3f + 2e-6f * fabsf(m));
-    if (!(second < line)) best = scan_exact(lr, a, pos, str, v_lo, v_hi);
-    else if (!(top < line)) best = make_key(exact_score(top_l, a.temperature, top_k), top_v);
+    const float m = max_block(top, redf);
+    if (fabsf(m) < kNoiseless) {
+      const float line = m - (2e-3f + 2e-6f * fabsf(m));
+      if (!(second < line)) best = scan_exact(lr, a, pos, str, v_lo, v_hi);
+      else if (!(top < line)) best = make_key(exact_score(top_l, a.temperature, top_k), top_v);
+    } else {                                        // the whole workgroup, as m is
+      float hi = -INFINITY;
+      best = scan_noiseless<T, VEC>(lr, a, v_lo, v_hi, hi);
+      __syncthreads();                              // every thread has read redf
+      if (fabsf(max_block(hi, redf)) < kNoiseless) best = scan_exact(lr, a, pos, str, v_lo, v_hi);
+    }
   } else {
     best = scan_exact(lr, a, pos, str, v_lo, v_hi);
   }

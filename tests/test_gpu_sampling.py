@@ -121,3 +121,68 @@ def test_infinities_and_nan_with_noise():
     for logits in (x, x[:, :1499].contiguous(), x.to(torch.bfloat16)):
         got = sample_tokens(logits, 0.7, 1, list(range(6)), [0] * 6).cpu().tolist()
         assert got[:5] == [1300, 0, 0, 700, 9] and got[5] < 3
+
+
+LOWEST = {torch.float32: torch.finfo(torch.float32).min, torch.bfloat16: torch.finfo(torch.bfloat16).min}
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("mask", [-float("inf"), "lowest", -1e9, -5e8, -1e4])
+@pytest.mark.parametrize("vocab", [30000, 20001])       # four chunks and three; whole vectors and not
+def test_masked_vocabularies(vocab, dtype, mask):
+    """A few entries left of a row, the others at a mask's value, so that most
+    chunks hold nothing but it; and a row that is masked altogether."""
+    log(f"sampling masked vocab={vocab} {dtype} {mask}")
+    rng = np.random.default_rng(vocab)
+    n, value = 4, LOWEST[dtype] if mask == "lowest" else mask
+    x = np.full((n, vocab), value, np.float64)
+    x[0, rng.integers(vocab, size=50)] = rng.standard_normal(50) * 3
+    x[1, [17, vocab - 1]] = 1.25, 1.25
+    x[2, 9000:9010] = -3e8                              # large, and not the mask
+    t = torch.from_numpy(x.astype(np.float32)).cuda().to(dtype)
+    l64 = t.float().cpu().numpy().astype(np.float64)
+    ws = torch.empty(sample_workspace_bytes(n, vocab), dtype=torch.uint8, device="cuda")
+    for T in (0.7, 1.0, 1.6, 4.0):
+        for w in (None, ws):
+            got = sample_tokens(t, T, 99, [3, 1, 4, 1], [5, 9, 2, 6], workspace=w).cpu().numpy()
+            with np.errstate(over="ignore", invalid="ignore"):
+                _check(got, l64, T, 99, [3, 1, 4, 1], [5, 9, 2, 6])
+
+
+def test_scores_that_overflow_one_over_the_temperature():
+    """T below 2^-128: 1 / T is infinite, l / T of small logits is not and the
+    noise decides."""
+    rng = np.random.default_rng(3)
+    T = 1e-39
+    x = torch.from_numpy((rng.standard_normal((3, 1000)) * 2e-39).astype(np.float32))
+    x[1] = 0.0
+    x[2, 5:] = -float("inf")
+    got = sample_tokens(x.cuda(), T, 8, [1, 2, 3], [4, 5, 6]).cpu().numpy()
+    _check(got, x.numpy().astype(np.float64), T, 8, [1, 2, 3], [4, 5, 6])
+
+
+def test_masked_rows_take_no_longer_than_dense_ones():
+    """Fifty entries left of 128256: the chunks without one cost a second, cheap
+    look at the logits (1.1 of a dense row), not a second scan (1.6)."""
+    g = torch.Generator(device="cuda").manual_seed(1)
+    n, vocab = 256, 128256
+    dense = (2 * torch.randn(n, vocab, device="cuda", generator=g)).to(torch.bfloat16)
+    keep = torch.randint(vocab, (n, 50), device="cuda", generator=g)
+    ws = torch.empty(sample_workspace_bytes(n, vocab), dtype=torch.uint8, device="cuda")
+    out = torch.empty(n, dtype=torch.int32, device="cuda")
+
+    def us(x):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(20):
+            sample_tokens(x, 0.7, 5, list(range(n)), [0] * n, out=out, workspace=ws)
+        b.record()
+        torch.cuda.synchronize()
+        return a.elapsed_time(b) / 20 * 1e3
+    for value in (-float("inf"), LOWEST[torch.bfloat16], -1e9):
+        masked = torch.full_like(dense, value).scatter_(1, keep, dense.gather(1, keep))
+        us(dense), us(masked)
+        pairs = [(us(dense), us(masked)) for _ in range(7)]
+        ratio = sorted(m / d for d, m in pairs)[3]
+        log(f"masked with {value}: {ratio:.2f} of a dense row's time")
+        assert ratio < 1.35
