@@ -15,7 +15,7 @@ from typing import Dict, List, Optional, Sequence
 import torch
 
 from . import _native as N
-from .pool import KVPool, gemm_bf16, gemm_bf16_multi, gemm_silu_bf16
+from .pool import KVPool, _dev_ptr, gemm_bf16, gemm_bf16_multi, gemm_silu_bf16
 
 
 def _stream(stream):
@@ -39,9 +39,13 @@ def rope_(x: torch.Tensor, positions: torch.Tensor, theta: float, stream=None) -
 
 def rope_qk_(q: torch.Tensor, k: torch.Tensor, positions: torch.Tensor, theta: float, stream=None) -> None:
     """``rope_`` of q [n, n_q_heads, d] and k [n, n_kv_heads, d] in one launch."""
-    assert positions.dtype == torch.int32 and positions.is_cuda
-    N.check(N.lib.pgsr_rope_qk_bf16(q.shape[0], q.shape[1], k.shape[1], q.shape[2], q.data_ptr(), k.data_ptr(),
-                                    positions.data_ptr(), float(theta), _stream(stream)))
+    n, hq, d = q.shape
+    if tuple(k.shape[::2]) != (n, d) or positions.numel() < n:
+        raise ValueError(f"q is {tuple(q.shape)}, k {tuple(k.shape)}, positions {tuple(positions.shape)}")
+    dv = q.device.index
+    qp, kp = (_dev_ptr(t, torch.bfloat16, name, dv, n * t.shape[1] * d) for t, name in ((q, "q"), (k, "k")))
+    N.check(N.lib.pgsr_rope_qk_bf16(n, hq, k.shape[1], d, qp, kp, _dev_ptr(positions, torch.int32, "positions", dv),
+                                    float(theta), _stream(stream)))
 
 
 def silu_mul(gate_up: torch.Tensor, out: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
