@@ -172,7 +172,17 @@ hipError_t launch_rope(int32_t n, int32_t heads0, int32_t heads1, int32_t d, voi
                        const int32_t* pos, double theta, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   const double log2_theta = log2(theta);
-  if (d % 16 == 0 && d <= 2 * kRopeHalf && (((uintptr_t)x0 | (uintptr_t)x1) & 15) == 0) {
+  // The row kernel shares a token's angles among its heads and takes Q and K in one
+  // launch, but one workgroup walks all heads of a token, 256 accesses of 8 pairs at a
+  // time (0.9 us each; us a call on the device, rows and a pair per thread).  One
+  // tensor of up to 2^17 pairs or of one head has nothing to gain (1 token x 64
+  // heads of 128: 4.0, 2.6; 100 x 8: 3.2, 2.6; 100 x 32: 3.3, 3.5), and past three
+  // accesses a thread it takes a hundred tokens to win again (1 x 4096 heads: 131,
+  // 3.5; 100 x 4096: 153, 131; 600 x 512: 31, 103).  A launch counts its threads in 32 bits.
+  const int64_t heads = (int64_t)heads0 + heads1, per_token = heads * (d / 16);
+  const bool share = heads1 > 0 || (heads > 1 && n * heads * (d / 2) > (1 << 17));
+  if (d % 16 == 0 && d <= 2 * kRopeHalf && (((uintptr_t)x0 | (uintptr_t)x1) & 15) == 0 && share &&
+      (per_token <= 768 || (n >= 128 && per_token < (1 << 28))) && n < (1 << 26)) {
     if (n >= 1024)
       hipLaunchKernelGGL(rope_rows_kernel<4>, dim3((n + 3) / 4), dim3(kThreads), 0, s, n, heads0, heads1, d,
                          (uint16_t*)x0, (uint16_t*)x1, pos, log2_theta);

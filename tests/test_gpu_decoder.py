@@ -190,3 +190,55 @@ def test_captured_restore_replay_matches_eager():
         assert torch.equal(full[P:], want)
         assert dec.crop([1], [0]) == 0
         torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("n,hq,hkv,d", [(1, 88, 8, 128), (1, 89, 8, 128), (5, 512, 64, 64), (127, 300, 20, 64),
+                                        (128, 300, 20, 64), (3, 4096, 0, 16), (64, 32, 0, 128), (65, 32, 0, 128),
+                                        (4100, 1, 0, 128)])
+def test_rope_of_many_heads(n, hq, hkv, d):
+    """Both sides of the lines between a workgroup per token and a pair per
+    thread (accesses to a token, tokens, pairs of one tensor, one head), bitwise
+    equal to the latter, which takes tensors off the 16-byte boundary."""
+    g = torch.Generator(device="cuda").manual_seed(hq + n)
+    log(f"rope n={n} heads={hq}/{hkv} d={d}")
+    q, k = (torch.randn(n, h, d, device="cuda", generator=g).to(torch.bfloat16) for h in (hq, hkv))
+    pos = torch.randint(0, 131072, (n,), dtype=torch.int32, device="cuda", generator=g)
+
+    def shifted(x):
+        t = torch.empty(x.numel() + 1, dtype=x.dtype, device="cuda")[1:].view(x.shape)
+        return t.copy_(x)
+    want_q, want_k = rope_(shifted(q), pos, 5e5), rope_(shifted(k), pos, 5e5) if hkv else k
+    if hkv:
+        rope_qk_(q, k, pos, 5e5)
+    else:
+        rope_(q, pos, 5e5)
+    assert torch.equal(q, want_q) and torch.equal(k, want_k)
+
+
+def test_rope_of_few_tokens_and_many_heads_is_not_a_serial_walk():
+    x, pos = torch.zeros(1, 4096, 128, dtype=torch.bfloat16, device="cuda"), torch.ones(1, dtype=torch.int32, device="cuda")
+    off = torch.zeros(x.numel() + 1, dtype=torch.bfloat16, device="cuda")[1:].view(x.shape)
+
+    def us(t):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(30):
+            rope_(t, pos, 5e5)
+        b.record()
+        torch.cuda.synchronize()
+        return a.elapsed_time(b) / 30 * 1e3
+    us(x), us(off)
+    pairs = [(us(x), us(off)) for _ in range(5)]
+    log(f"rope 1 x 4096 heads: on the boundary, off it (us) {pairs}")
+    assert sorted(a / b for a, b in pairs)[2] < 3         # 16 when one workgroup took them all
+
+
+def test_rope_of_more_tokens_than_one_grid_of_rows():
+    """2^26 + 5 tokens: a workgroup for every four of them is 2^32 threads."""
+    n, d = (1 << 26) + 5, 16
+    x = torch.ones(n, 1, d, dtype=torch.bfloat16, device="cuda")
+    pos = torch.arange(n, dtype=torch.int32, device="cuda")
+    rope_(x, pos, 5e5)
+    for s in (slice(0, 9), slice(n // 2, n // 2 + 9), slice(n - 9, n)):
+        part = torch.ones(9, 1, d, dtype=torch.bfloat16, device="cuda")
+        assert torch.equal(x[s], rope_(part, pos[s].contiguous(), 5e5))
