@@ -545,7 +545,7 @@ hipError_t launch_attn_bf16_pipe(const AttnArgs& a, int waves, bool fp8, hipStre
   if (a.n <= 0 || a.n_tiles <= 0) return hipSuccess;
   if (!attn_bf16_pipe_eligible(a.head_dim, a.n_q_heads / a.n_kv_heads)) return hipErrorInvalidValue;
   if (waves == 8) return fp8 ? launch_p_b<8, true>(a, s) : launch_p_b<8, false>(a, s);
-  if (waves == 4) return fp8 ? launch_p_b<4, true>(a, s) : launch_p_b<4, false>(a, s);
+  if (waves == 4 && fp8) return launch_p_b<4, true>(a, s);   // bf16: the four-wave kernel is faster there
   return hipErrorInvalidValue;
 }
 
