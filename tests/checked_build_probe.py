@@ -43,9 +43,9 @@ def episode():
     return W.draw_episode(np.random.default_rng(77), GEOM, "bf16", P, S, T)
 
 
-def fresh_pool(ep, ws=False):
+def fresh_pool(ep, ws=False, seqs=4):
     """A pool holding the contaminated run of seq 0, cropped to P (blocks 0..18 kept)."""
-    pool = KVPool(1, 32, 8, 128, n_blocks=96, max_seqs=4, max_blocks_per_seq=40, dtype=BF16,
+    pool = KVPool(1, 32, 8, 128, n_blocks=24 * seqs, max_seqs=seqs, max_blocks_per_seq=40, dtype=BF16,
                   workspace_bytes=workspace_bytes(32, 128, 64) if ws else 0)
     cq, ck, cv = (dev(ep.contaminated(x)) for x in ("q", "k", "v"))
     assert pool.replay(0, [0], [T], cq, ck, cv, torch.empty_like(cq), SCALE) == 0
@@ -93,6 +93,20 @@ def main():
         res[f"prefill_{kind}"] = pool.replay(0, [0], [S], q, k, v, o, SCALE)
         res[f"prefill_{kind}_msg"] = N.lib.pgsr_last_error().decode()
         pool.close()
+
+    # the default kernel of S tokens is the narrow one (13 workgroups to a KV head of 8); the wide one takes
+    # calls past 256 workgroups of its tiles of four waves: as many sequences, forks of the same prefix
+    log("case: corrupted prefix entry, wide prefill kernel")
+    pool = fresh_pool(ep, seqs=12)
+    assert pool.fork([0] * 11, list(range(1, 12))) == 0
+    corrupt(pool, 5, 3)
+    q, k, v, o = (torch.cat([t] * 12) for t in suffix(ep))
+    pool.set_clock_probe(4096)
+    pool.enable_timing(True)
+    res["prefill_wide"] = pool.replay(0, list(range(12)), [S] * 12, q, k, v, o, SCALE)
+    torch.cuda.synchronize()
+    res["prefill_wide_workgroups"] = int((pool._clk.view(-1, 4)[:, 1] != 0).sum())
+    pool.close()
 
     log("case: corrupted prefix entry, decode (one token, split keys)")
     pool = fresh_pool(ep, ws=True)

@@ -1,7 +1,7 @@
 """The checked build (lib/libpgsr_checked.so, compiled with PGSR_CHECKED):
 block ids that device metadata written outside the library puts out of range
 make every pool call that reads them return PGSR_ERANGE, on each path that
-reads a table or the free stack (three bf16 prefill kernels, decode, crop,
+reads a table or the free stack (the four bf16 prefill kernels, decode, crop,
 restore + replay in one call, fork), without any access outside the pool; an
 intact replay gives the same bits as the default build.
 
@@ -49,7 +49,9 @@ def test_checked_build_reports_out_of_range_block_ids(tmp_path):
     assert res["intact"] == N.OK and res["after"] == N.OK
     assert np.array_equal(np.load(out), want), "checked build differs from the default build"
     assert res["after_equal"], "a call after an error differs from the first intact call"
-    for case in ("prefill_auto", "prefill_pipelined", "prefill_four_wave", "decode", "crop",
+    for case in ("prefill_auto", "prefill_pipelined", "prefill_four_wave", "prefill_wide", "decode", "crop",
                  "restore_replay", "fork"):
         assert res[case] == N.ERANGE, (case, res[case])
     assert "block id outside" in res["prefill_auto_msg"]
+    # 12 sequences x 2 tiles of 64 tokens x 8 heads: the wide kernel's grid
+    assert res["prefill_wide_workgroups"] == 12 * 2 * 8

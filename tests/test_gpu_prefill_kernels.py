@@ -1,14 +1,17 @@
-"""The bf16 prefill kernels for head_dim 128 and GQA groups dividing 32 (the
-wide kernel: one wave per SIMD, 64 rows per wave, 16-token blocks; the
-software-pipelined kernel: two waves per SIMD) against the four-wave kernel and
-the fp64 oracle.  All kernels take every query row through the same sequence
-of operations, so their outputs must agree bit for bit; each must also meet
-the bf16 tolerance against the oracle.  Cases cover every group size the pipelined kernel takes, block sizes
-16 / 32 / 64, crops not aligned to a block with NaN-poisoned tail slots,
-suffixes shorter than one query tile, tiles that straddle the diagonal, and
-several sequences of different lengths in one call; then the default kernel
-on more shapes against the oracle and against the full reset of every
-sequence in one call (bitwise)."""
+"""The bf16 prefill kernels for head_dim 128 (the wide kernel: one wave per SIMD,
+64 rows per wave, 16-token blocks; the narrow one: 32 rows per wave, for calls
+that leave CUs idle; the software-pipelined kernel: two waves per SIMD) against
+the four-wave kernel and the fp64 oracle.  All kernels take every query row
+through the same sequence of operations, so their outputs must agree bit for
+bit; each must also meet the bf16 tolerance against the oracle.  CASES and
+DEFAULT_CASES cover every group size that divides 32, block sizes 16 / 32 / 64,
+crops not aligned to a block with NaN-poisoned tail slots, suffixes shorter
+than one query tile, tiles that straddle the diagonal, and several sequences of
+different lengths in one call, against the oracle and the full reset of every
+sequence in one call (bitwise); most are small, so by default they run the narrow
+kernel (16-token blocks) or the four-wave one.  TAKEN has calls past the lines
+of the dispatch, for the wide and the pipelined kernel and every group, and
+tells by the number of workgroups which kernel ran."""
 import numpy as np
 import pytest
 import torch
@@ -23,9 +26,10 @@ def _blocks(n, B):
     return -(-n // B)
 
 
-def _run(kind, geom, eps, B, scale):
+def _run(kind, geom, eps, B, scale, ran=None):
     """Contaminated prefill, poisoned crop, then one replay call over all
-    episodes; returns the per-episode outputs."""
+    episodes; returns the per-episode outputs (``ran`` gets the number of
+    workgroups that wrote the clock probe)."""
     nb = sum(_blocks(e.t_contaminated, B) + _blocks(e.t_sanitized, B) for e in eps) + 4
     mbps = max(_blocks(max(e.t_contaminated, e.t_sanitized), B) for e in eps) + 2
     pool = make_pool(geom, "bf16", nb, len(eps), mbps, block_size=B)
@@ -34,8 +38,9 @@ def _run(kind, geom, eps, B, scale):
         contaminated_then_crop(pool, e, i, scale, poison=True)
     q, k, v = (torch.cat([dev(getattr(e, x)[e.prefix:], "bf16") for e in eps]) for x in ("q", "k", "v"))
     o = torch.empty_like(q)
-    assert pool.replay(0, list(range(len(eps))), [e.suffix for e in eps], q, k, v, o, scale) == 0
-    torch.cuda.synchronize()
+    n = probed_workgroups(pool, lambda: pool.replay(0, list(range(len(eps))), [e.suffix for e in eps], q, k, v, o, scale))
+    if ran is not None:
+        ran.append(n)
     out, off = [], 0
     for e in eps:
         out.append(o[off:off + e.suffix])
@@ -68,7 +73,7 @@ def test_pipelined_equals_four_wave_and_oracle(hq, hkv, B, ps):
     rng = np.random.default_rng(hq * 7919 + B + sum(p for p, _ in ps))
     eps = [W.draw_episode(rng, geom, "bf16", P, S, P + S + 3) for P, S in ps]
     scale = 128 ** -0.5
-    auto = _run("auto", geom, eps, B, scale)          # the wide kernel where B = 16
+    auto = _run("auto", geom, eps, B, scale)          # narrow or wide where B = 16, else mostly four-wave
     pipe = _run("pipelined", geom, eps, B, scale)
     four = _run("four_wave", geom, eps, B, scale)
     for e, a, p, f in zip(eps, auto, pipe, four):
@@ -150,21 +155,23 @@ def test_pipelined_full_reset_equals_replay_at_8b_crop():
     assert_close(got.float().cpu().numpy(), ref, "bf16", "8B crop, sampled rows")
 
 
-@pytest.mark.parametrize("P,S", [(130700, 100), (130900, 100)])
-def test_longest_sequences_for_the_lds_block_table(P, S):
-    """A sequence at the wide kernel's limit (130816 keys: a workgroup's copy
-    of the block table fills its LDS share) and one just past it (the host
-    then runs the pipelined kernel): the default kernel bitwise against the
-    four-wave one, and sampled rows against the oracle."""
+@pytest.mark.parametrize("P,S,tile_waves", [(130700, 100, 2), (129786, 1030, 8), (130900, 100, 0), (129890, 1030, 8)])
+def test_longest_sequences_for_the_lds_block_table(P, S, tile_waves):
+    """Sequences at the limit of the narrow and the wide kernel (130816 keys: a
+    workgroup's copy of the block table fills its LDS share) and just past it
+    (the host then runs the four-wave and the pipelined kernel): the default kernel
+    bitwise against the four-wave one, and sampled rows against the oracle."""
     geom = W.AttnGeometry(32, 8, 128)
     log(f"longest sequences: P={P} S={S}")
     rng = np.random.default_rng(P)
     eps = [W.draw_episode(rng, geom, "bf16", P, S, P + S + 3)]
     scale = 128 ** -0.5
-    auto = _run("auto", geom, eps, 16, scale)[0]
+    ran = []
+    auto = _run("auto", geom, eps, 16, scale, ran)[0]
+    assert ran[0] == (-(-S // (8 * tile_waves)) * 8 if tile_waves else 0)
     four = _run("four_wave", geom, eps, 16, scale)[0]
     assert torch.equal(auto, four), f"default and four-wave kernels differ (P={P}, S={S})"
-    rows = np.arange(0, S * geom.n_q_heads, 97)
+    rows = np.arange(0, S * geom.n_q_heads, 97 if S < 1000 else 997)
     ref = oracle_suffix(eps[0], scale, rows=rows)
     got = auto.reshape(-1, 128)[torch.from_numpy(rows).cuda()].float().cpu().numpy()
     assert_close(got, ref, "bf16", f"P={P} S={S}")
@@ -186,7 +193,7 @@ def test_longest_sequences_for_the_lds_block_table(P, S):
     (28, 4, 16, [(100, 700), (3, 20)], 0),             # four waves
     (28, 4, 16, [(500, 1100)], 0),                     # wide
     (20, 4, 16, [(129, 50)], 0),                       # G = 5
-    (28, 4, 32, [(129, 900)], 0),                      # pipelined with padded rows
+    (28, 4, 32, [(129, 900)], 0),                      # four-wave (57 tiles of 4 waves x 4 heads = 228)
     (28, 4, 64, [(64, 40)], 0),                        # four-wave
     (32, 8, 16, [(900, 40)], 40),                      # split keys
     (28, 4, 16, [(2000, 130)], 130),
@@ -263,6 +270,23 @@ TAKEN = [
     ("bf16", 28, 4, 16, [(832, 509)] * 4, "wide", 8),              # 17
     ("bf16", 28, 4, 32, [(900, 700)] * 3, "pipelined", 8),
     ("fp8", 32, 8, 16, [(1500, 600), (900, 1000)], "pipelined", 8),
+    # every group in the wide kernel, past the 256 workgroups of the narrow one; crops inside a block
+    ("bf16", 64, 64, 16, [(45, 530), (3, 20)], "wide", 8),
+    ("bf16", 128, 64, 16, [(77, 270)], "wide", 8),
+    ("bf16", 128, 32, 16, [(300, 257), (17, 64)], "wide", 8),
+    ("bf16", 64, 8, 16, [(301, 520), (0, 33)], "wide", 8),
+    ("bf16", 256, 32, 16, [(129, 140)], "wide", 8),
+    ("bf16", 256, 16, 16, [(65, 140)], "wide", 8),
+    ("bf16", 256, 8, 16, [(129, 135), (1000, 1)], "wide", 8),
+    ("bf16", 200, 40, 16, [(700, 192)], "wide", 8),
+    # and in the pipelined one by default
+    ("bf16", 64, 64, 32, [(45, 530), (3, 20)], "pipelined", 8),
+    ("bf16", 128, 64, 64, [(77, 270)], "pipelined", 8),
+    ("bf16", 128, 32, 32, [(300, 257), (17, 64)], "pipelined", 8),
+    ("bf16", 256, 32, 64, [(129, 140)], "pipelined", 8),
+    ("bf16", 256, 16, 32, [(65, 140)], "pipelined", 8),
+    ("bf16", 256, 8, 64, [(129, 135), (1000, 1)], "pipelined", 8),
+    ("bf16", 224, 32, 32, [(701, 150)], "pipelined", 8),
 ]
 
 
