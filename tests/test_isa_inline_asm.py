@@ -1,6 +1,7 @@
 """Machine-code checks of the inline assembly in the kernels that issue
-global->LDS loads (the wide prefill kernel and the wide GEMM; host only: the
-kernels are compiled to gfx950 assembly, nothing runs).
+global->LDS loads (the wide and the narrow prefill kernel, the 256 x 256 and the
+ring GEMM, every instantiation; host only: the kernels are compiled to gfx950
+assembly with the library's options, nothing runs).
 
 Their tile requests are inline assembly that writes M0 with an SALU
 instruction and then issues a global->LDS load.  Two properties keep them
@@ -20,6 +21,8 @@ import subprocess
 
 import pytest
 
+from paper_2609_04875_amd import build
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2609_04875_amd", "csrc")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -31,25 +34,38 @@ SCC_WRITE = re.compile(
     r"|s_lshl\d_add_u32|s_(and|or)_saveexec_b64)\b")
 
 
-KERNELS = {"attn": ("attn_bf16_wide.hip", "attn_bf16_wide_kernel", 24),
-           "gemm": ("gemm_bf16_wide.hip", "gemm_bf16_wide_kernel", 32)}
+# source, kernel name, instantiations, requests of the smallest one (the prologue's and the loop's tiles)
+KERNELS = {"attn_wide": ("attn_bf16_wide.hip", "attn_bf16_wide_kernel", 2, 24),
+           "attn_narrow": ("attn_bf16_narrow.hip", "attn_bf16_narrow_kernel", 2, 24),
+           "gemm_wide": ("gemm_bf16_wide.hip", "gemm_bf16_wide_kernel", 1, 32),
+           "gemm_dma": ("gemm_bf16_dma.hip", "gemm_bf16_dma_kernel", 32, 6)}
 
 
-@pytest.fixture(scope="module", params=sorted(KERNELS))
-def wide_asm(request, tmp_path_factory):
-    if not shutil.which(HIPCC) and not os.path.exists(HIPCC):
-        pytest.skip("hipcc not available")
-    src, kernel, min_requests = KERNELS[request.param]
-    out = tmp_path_factory.mktemp("isa") / (request.param + ".s")
+def _instantiations(name, out):
+    src, kernel, _, _ = KERNELS[name]
     cmd = [HIPCC, "-O3", "-std=c++17", "--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang",
-           "-packed-fp32-ops", f"-I{os.path.join(ROOT, 'include')}", f"-I{CSRC}", "-x", "hip",
+           "-packed-fp32-ops", *build.EXTRA.get(src, []), f"-I{os.path.join(ROOT, 'include')}", f"-I{CSRC}", "-x", "hip",
            "--cuda-device-only", "-S", os.path.join(CSRC, src), "-o", str(out)]
     subprocess.run(cmd, check=True, capture_output=True)
     lines = [ln.split(";")[0].strip() if not ln.strip().startswith(";;#ASM") else ln.strip()
              for ln in out.read_text().splitlines()]
-    start = next(i for i, ln in enumerate(lines) if re.match(rf"^_Z\w*{kernel}\w*:", ln))
-    end = next(i for i in range(start, len(lines)) if lines[i].startswith("s_endpgm"))
-    return lines[start:end + 1], min_requests
+    found = {}
+    for start, ln in enumerate(lines):
+        if re.match(rf"^_Z\w*{kernel}\w*:", ln):
+            # to the next function: an early exit ends the program before its last line
+            stop = next((i for i in range(start + 1, len(lines)) if lines[i].startswith(".Lfunc_end")), len(lines))
+            found[ln.rstrip(":")] = lines[start:stop]
+    return found
+
+
+@pytest.fixture(scope="module", params=sorted(KERNELS))
+def kernels(request, tmp_path_factory):
+    """Assembly lines of every instantiation of a kernel, as the library is compiled."""
+    if not shutil.which(HIPCC) and not os.path.exists(HIPCC):
+        pytest.skip("hipcc not available")
+    found = _instantiations(request.param, tmp_path_factory.mktemp("isa") / (request.param + ".s"))
+    assert len(found) == KERNELS[request.param][2], sorted(found)
+    return found, KERNELS[request.param][3]
 
 
 def _asm_blocks(lines):
@@ -63,36 +79,47 @@ def _asm_blocks(lines):
     return blocks
 
 
-def test_requests_present(wide_asm):
-    lines, min_requests = wide_asm
-    n = sum(1 for ln in lines if ln.startswith("global_load_lds_dwordx4"))
-    assert n >= min_requests, f"expected the prologue's and the loop's tile requests, found {n}"
+def test_requests_present(kernels):
+    for name, lines in kernels[0].items():
+        n = sum(1 for ln in lines if ln.startswith("global_load_lds_dwordx4"))
+        assert n >= kernels[1], f"{name}: expected the prologue's and the loop's tile requests, found {n}"
 
 
-def test_no_compiler_scc_value_across_a_request(wide_asm):
-    wide_asm, _ = wide_asm
+def test_no_compiler_scc_value_across_a_request(kernels):
     bad = []
-    for a, b in _asm_blocks(wide_asm):
-        if not any(SCC_WRITE.match(ln) for ln in wide_asm[a + 1:b]):
-            continue
-        for i in range(b + 1, len(wide_asm)):
-            ln = wide_asm[i]
-            if ln.startswith(";;#ASMSTART") or ln.endswith(":"):
-                break                                # another block or a label: checked on its own
-            if SCC_READ.match(ln):
-                bad.append(f"{ln!r} reads SCC set by the inline assembly ending {i - b} lines above")
-                break
-            if SCC_WRITE.match(ln):
-                break
+    for name, asm in kernels[0].items():
+        for a, b in _asm_blocks(asm):
+            if not any(SCC_WRITE.match(ln) for ln in asm[a + 1:b]):
+                continue
+            for i in range(b + 1, len(asm)):
+                ln = asm[i]
+                if ln.startswith(";;#ASMSTART") or ln.endswith(":"):
+                    break                            # another block or a label: checked on its own
+                if SCC_READ.match(ln):
+                    bad.append(f"{name}: {ln!r} reads SCC set by the inline assembly ending {i - b} lines above")
+                    break
+                if SCC_WRITE.match(ln):
+                    break
     assert not bad, "\n".join(bad[:5])
 
 
-def test_wait_state_between_m0_write_and_lds_load(wide_asm):
-    wide_asm, _ = wide_asm
+def test_wait_state_between_m0_write_and_lds_load(kernels):
     bad = []
-    for a, b in _asm_blocks(wide_asm):
-        body = [ln for ln in wide_asm[a + 1:b] if ln]
-        for j, ln in enumerate(body):
-            if ln.startswith("global_load_lds") and j > 0 and re.match(r"^s_\w+ m0\b", body[j - 1]):
-                bad.append(" / ".join(body))
+    for name, asm in kernels[0].items():
+        for a, b in _asm_blocks(asm):
+            body = [ln for ln in asm[a + 1:b] if ln]
+            for j, ln in enumerate(body):
+                if ln.startswith("global_load_lds") and j > 0 and re.match(r"^s_\w+ m0\b", body[j - 1]):
+                    bad.append(f"{name}: " + " / ".join(body))
     assert not bad, "\n".join(bad[:3])
+
+
+def test_m0_is_written_by_the_requests_alone(kernels):
+    """The requests set M0 themselves each time; compiler code that used it (an
+    LDS address, an indexed register) would find another value in it."""
+    for name, asm in kernels[0].items():
+        inside = set()
+        for a, b in _asm_blocks(asm):
+            inside.update(range(a, b + 1))
+        outside = [ln for i, ln in enumerate(asm) if i not in inside and re.search(r"\bm0\b", ln)]
+        assert not outside, f"{name}: {outside[:3]}"
