@@ -109,6 +109,21 @@ class Setup:
     def restore(self) -> None:
         self.pool.load_meta(self.saved)
 
+    def probed_workgroups(self) -> int:
+        """Workgroups of the (first) replay call that stamped the clock probe."""
+        self.restore()
+        n = self.chunk or sum(self.S)
+        self.pool.set_clock_probe(1 << 16)
+        self.pool.enable_timing(True)
+        if self.pool.restore_replay(0, self.seqs, self.P, [self.chunk] if self.chunk else self.S, self.q[:n], self.k[:n],
+                                    self.v[:n], self.o[:n], self.w.scale):
+            raise RuntimeError("restore + replay failed")
+        self.torch.cuda.synchronize()
+        stamped = int((self.pool._clk.view(-1, 4)[:, 1] != 0).sum())
+        self.pool.enable_timing(False)
+        self.pool.set_clock_probe(0)
+        return stamped
+
     def step(self, ev=None) -> None:
         """Restore (crop) + replay: one restore + replay call for the first (or
         only) replay call of the step, plain replay calls for the remaining
@@ -359,6 +374,38 @@ def bench_stack(args):
     }
     print(json.dumps(result), flush=True)
     return 0
+
+
+def prefill_kernel(w, n_blocks, P, S, kind, workspace):
+    """(source, kernel, workgroups that stamp the clock probe) of the kernel that
+    the library's rule takes for one prefill call of ``S[i]`` tokens after
+    ``P[i]`` each, for pools of fp32, head_dim 64, or groups that divide 32."""
+    g, B = w.geometry, w.block_size
+    G, d, hkv = g.n_q_heads // g.n_kv_heads, g.head_dim, g.n_kv_heads
+    if w.dtype == "f32":
+        return "attn_f32", f"attn_f32_kernel<{d}>", 0
+    four = "attn_bf16", f"attn_bf16_kernel<{d},4,{B}>", 0
+    if d != 128 or kind == "four_wave" or 32 % G:
+        return four
+    tiles = lambda waves: sum(-(-s // (waves * 32 // G)) for s in S) * hkv  # noqa: E731
+    keys, split_len = max(p + s for p, s in zip(P, S)), 0
+    n = min(32, -(-256 // tiles(8)), workspace // (sum(S) * g.n_q_heads * (d + 2) * 4)) if tiles(8) < 256 else 1
+    if n > 1:
+        split_len = -(-(-(-keys // n)) // 64) * 64
+    splits = -(-keys // split_len) if split_len else 1
+
+    def grid(waves):                     # a workgroup whose split starts past its tile's last key stamps nothing
+        t = waves * 32 // G
+        return hkv * sum(-(-(p + min(s, t0 + t)) // split_len) if split_len else 1
+                         for p, s in zip(P, S) for t0 in range(0, s, t))
+    if kind == "auto" and B == 16 and n_blocks * hkv * 4096 <= 1 << 32 and keys <= 130816:
+        for waves in (2, 4):
+            if tiles(waves) * splits <= 256:
+                return "attn_bf16_narrow", f"attn_bf16_narrow_kernel<{waves}>", grid(waves)
+        return "attn_bf16_wide", "attn_bf16_wide_kernel", grid(8)
+    if kind == "auto" and tiles(4) * splits <= 256:
+        return four
+    return "attn_bf16_pipe", f"attn_bf16_pipe_kernel<{B}>", grid(8)
 
 
 def traffic_profile_path(kernel_file: str, workload: str) -> str:
@@ -714,8 +761,8 @@ def main() -> int:
     ap.add_argument("--cpu-seconds", type=float, default=15.0)
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--prefill-kernel", choices=("auto", "pipelined", "four_wave"), default="auto",
-                    help="bf16 prefill kernel: wide, else pipelined, where they apply (auto); "
-                         "never the wide kernel (pipelined); four-wave")
+                    help="bf16 prefill kernel: by the cache and the size of the call (auto), "
+                         "pipelined, or four-wave")
     ap.add_argument("--calibrate-copy-mib", type=int, default=0,
                     help="after timing, copy this many MiB device-to-device (counter scaling)")
     args = ap.parse_args()
@@ -739,12 +786,11 @@ def main() -> int:
     st = Setup(args.workload)
     w, g, pool = st.w, st.w.geometry, st.pool
     pool.set_prefill_kernel(args.prefill_kernel)
-    # which bf16 prefill kernel the library runs (the host's selection rule)
-    fast = (w.dtype == "bf16" and g.head_dim == 128 and 32 % (g.n_q_heads // g.n_kv_heads) == 0)
-    wide = (fast and args.prefill_kernel == "auto" and w.block_size == 16
-            and pool.n_blocks * g.n_kv_heads * 4096 <= 1 << 32
-            and max(p + s for p, s in zip(st.P, st.S)) <= 130816)
-    pipe = fast and not wide and args.prefill_kernel in ("auto", "pipelined")
+    # the prefill kernel of the step's (first) call by the library's rule, and whether the probe saw its grid
+    kfile, kname, grid = prefill_kernel(w, pool.n_blocks, st.P, [st.chunk] if st.chunk else st.S, args.prefill_kernel,
+                                        0 if pool.workspace is None else pool.workspace.numel())
+    if grid != st.probed_workgroups():
+        kfile, kname = None, "a kernel that the benchmark does not know"
     single_call = st.calls_per_step == 1
     ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
     step_ms, attn_ms, append_ms, inst_ms = [], [], [], []
@@ -765,7 +811,7 @@ def main() -> int:
     clk_rate = None
     if single_call:
         pool.enable_timing(True)
-        if wide or pipe:      # shader clock of the same dispatches, read in-kernel
+        if grid:              # shader clock of the same dispatches, read in-kernel
             pool.set_clock_probe(1 << 16)
         for i in range(args.steps):
             st.restore()
@@ -776,7 +822,7 @@ def main() -> int:
             a_ms, t_ms = pool.last_times()
             append_ms.append(a_ms)
             attn_ms.append(t_ms)
-            if wide or pipe:
+            if grid:
                 ghz, cyc, tck = pool.last_clock()
                 clk_cycles += cyc
                 clk_ticks += tck
@@ -815,12 +861,10 @@ def main() -> int:
     attn_mean = float(np.mean(attn_ms))
     achieved = flops / (attn_mean * 1e-3) / 1e12
     peak = PEAK_TFLOPS[w.dtype]
-    kfile = (("attn_bf16_wide" if wide else "attn_bf16_pipe" if pipe else "attn_bf16")
-             if w.dtype == "bf16" else "attn_f32")
     # mean shader clock of the timed attention dispatches of this run (cycle and
     # reference counters read by every workgroup at its start and end)
     sclk = clk_cycles / clk_ticks * clk_rate if clk_ticks else None
-    traffic = measured_traffic(kfile, w.name)
+    traffic = measured_traffic(kfile, w.name) if kfile else None
     # crop: released table entries (each read, cleared, its count read and
     # written, then pushed) plus lengths and the stack top
     released = sum(-(-e.t_contaminated // w.block_size) - -(-e.prefix // w.block_size) for e in st.eps)
@@ -852,10 +896,7 @@ def main() -> int:
                      # a diagnostic: frac is taken at the nominal 2.4 GHz
                      "sclk_ghz": sclk,
                      "frac_at_sclk": None if sclk is None else achieved / (peak * sclk / 2.4),
-                     "kernel": ("attn_bf16_wide_kernel" if wide
-                                else "attn_bf16_pipe_kernel<16>" if pipe
-                                else f"attn_bf16_kernel<{g.head_dim},4,16>" if w.dtype == "bf16"
-                                else f"attn_f32_kernel<{g.head_dim}>"),
+                     "kernel": kname,
                      "flops_per_step": flops, "algorithmic_bytes_per_step": nbytes,
                      "kernel_ms": attn_mean, "kernel_launches_per_step": st.calls_per_step,
                      "algorithmic_GBps": nbytes / (attn_mean * 1e-3) / 1e9,

@@ -43,3 +43,19 @@ def test_prefix_bytes():
     keys = sum(32768 + 512 * c for c in range(8))
     assert bench.Setup.prefix_bytes(st) == keys * 8 * 128 * 2 * 2
     assert bench.Setup.prefix_bytes(st) == pytest.approx(1.1325e9, rel=1e-4)
+
+
+@pytest.mark.parametrize("name,P,S,kind,ws_tokens,kernel,grid", [
+    ("llama8b_p8189_s2048_bf16", [8189], [2048], "auto", 0, "attn_bf16_wide_kernel", 32 * 8),
+    ("llama8b_p8189_s2048_bf16", [8189], [1024], "auto", 0, "attn_bf16_narrow_kernel<4>", 32 * 8),
+    ("llama8b_p8189_s2048_bf16", [1228], [102], "auto", 0, "attn_bf16_narrow_kernel<2>", 7 * 8),
+    ("llama8b_p8189_s2048_bf16", [8189], [2048], "pipelined", 0, "attn_bf16_pipe_kernel<16>", 32 * 8),
+    ("llama8b_p8189_s2048_bf16", [8189], [2048], "four_wave", 0, "attn_bf16_kernel<128,4,16>", 0),
+    # 64 wide workgroups in 4 splits of 8320 keys: all tiles reach the fourth
+    ("long32k_chunk512_llama8b_bf16", [32768], [512], "auto", 512, "attn_bf16_wide_kernel", 8 * 8 * 4),
+    ("tiny_mha8_d64_p512_s128_f32", [512], [128], "auto", 128, "attn_f32_kernel<64>", 0),
+])
+def test_prefill_kernel_of_a_call(name, P, S, kind, ws_tokens, kernel, grid):
+    w = W.workload(name)
+    ws = 16 * ws_tokens * w.geometry.n_q_heads * (w.geometry.head_dim + 2) * 4
+    assert bench.prefill_kernel(w, 2000, P, S, kind, ws)[1:] == (kernel, grid)
