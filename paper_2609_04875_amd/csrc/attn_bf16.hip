@@ -380,10 +380,10 @@ attn_bf16_kernel(AttnArgs a, const int32_t* __restrict__ tables, const uint16_t*
 // summed in increasing s.  16 threads per row, 8 columns each.  The partials
 // are read kGroup splits at a time, all loads of a group issued before any is
 // used, so a row with many splits (a decode step) waits on few round trips;
-// the sums still run in increasing s.  Decode steps and fp32 calls with more than 8
-// splits take groups of 16 (a short step has about 20: two round trips, not three;
-// the small fp32 episode 17.7 against 18.3 us);
-// the others, with more rows and 9 or 10 splits, lose 0.4 us by them.
+// the sums still run in increasing s.  Decode steps and fp32 calls with more than
+// 8 splits take groups of 16 (a short step has about 20: two round trips, not
+// three; the small fp32 episode 17.7 against 18.3 us); the others, with more rows
+// and 9 or 10 splits, lose 0.4 us by them.
 template <int D, int kGroup, typename TO>
 __global__ void __launch_bounds__(256) split_combine_kernel(AttnArgs a, TO* __restrict__ og) {
   constexpr int TPR = D / 8;                       // threads per row
@@ -406,8 +406,8 @@ __global__ void __launch_bounds__(256) split_combine_kernel(AttnArgs a, TO* __re
   float L = 0.f;
   f32x4 o0 = {0, 0, 0, 0}, o1 = {0, 0, 0, 0};
   if (ns <= kGroup) {
-    // one group (every decode call): all loads in one round trip, then the
-    // same max, weights and sums in the same order as the general loop below
+    // one group: all loads in one round trip, then the same max, weights and
+    // sums in the same order as the general loop below
     float mg[kGroup], lg[kGroup];
     f32x4 a0[kGroup], a1[kGroup];
 #pragma unroll

@@ -8,9 +8,9 @@
 // one 32-row block of (token, head) query rows (the last rows are padding where
 // G does not divide 32), and the two waves of a SIMD interleave their matrix
 // products with each other's softmax arithmetic.  Three 35 KB LDS tile buffers
-// keep one workgroup per CU.  NW = 4 is for calls that leave CUs idle: half the
-// rows, a shorter step (FP8, 32 query / 8 KV heads, 1024 tokens against 8189:
-// 178 us, eight waves 236, four-wave kernel 209).
+// keep one workgroup per CU.  NW = 4 is for FP8 calls that leave CUs idle: half the
+// rows, a shorter step (32 query / 8 KV heads, 1024 tokens against 8189: 178 us,
+// eight waves 236, four-wave kernel 209).
 //
 // FP8 cache (E4M3 codes): the gathers fetch 8 bytes where the bf16 ones fetch 16,
 // and the codes widen to bf16 exactly before the LDS store; the K scale rides
@@ -545,7 +545,7 @@ hipError_t launch_attn_bf16_pipe(const AttnArgs& a, int waves, bool fp8, hipStre
   if (a.n <= 0 || a.n_tiles <= 0) return hipSuccess;
   if (!attn_bf16_pipe_eligible(a.head_dim, a.n_q_heads / a.n_kv_heads)) return hipErrorInvalidValue;
   if (waves == 8) return fp8 ? launch_p_b<8, true>(a, s) : launch_p_b<8, false>(a, s);
-  if (waves == 4 && fp8) return launch_p_b<4, true>(a, s);   // bf16: the four-wave kernel is faster there
+  if (waves == 4 && fp8) return launch_p_b<4, true>(a, s);   // bf16 calls that leave CUs idle take other kernels
   return hipErrorInvalidValue;
 }
 

@@ -131,8 +131,13 @@ attn_decode_kernel(AttnArgs a, const int32_t* __restrict__ tables, const uint16_
   // Non-temporal where one instruction takes whole lines (FP8, 16 slots: 32
   // rows of 16 bytes in a run), which then pass the first-level cache without
   // taking lines of it: 32 ragged sequences 112.7 against 126.2 us (5.3 TB/s),
-  // 48 x 4000 keys 82 against 97.  K, and V in longer rows, reach a line in
-  // several instructions and lose (K: 155 us, bf16 303 against 190).
+  // 48 x 4000 keys 82 against 97.  From HBM, with the other layers' caches read
+  // since the last pass, every size gains (4 x 16000 57 against 69, 8 x 4000 37
+  // against 42); one layer's cache of less than 256 MB read again and again stays in
+  // the memory-side cache and gains nothing or loses up to a tenth (38 against 36.6,
+  // 27.6 both, 30000 keys of 4 KV heads 48 against 44).  K, and V in longer
+  // rows, reach a line in several instructions and lose (K: 155 us, bf16 303
+  // against 190).
   auto load_v = [&](int kb, int idv) {
     const auto* vp = vc + ((head_base + (int64_t)idv * hkv) * D + r) * B + v_key(kb) % B;
 #pragma unroll

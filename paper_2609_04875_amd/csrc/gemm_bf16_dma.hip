@@ -19,7 +19,7 @@
 // is 8 rows x 128 bytes, 1 KB of contiguous LDS with lane l's 16 bytes at byte
 // 16 l; chunk c of row j is fetched by the lane of slot c ^ ((j / 2) mod 8), so
 // the 16 rows of an operand read fall on all 64 banks.  A request carries no
-// register, so a workgroup keeps NST - 1 stages (28 to 96 KB) in flight.  Per
+// register, so a workgroup keeps NST - 1 stages (48 to 120 KB) in flight.  Per
 // stage a wave waits for its own requests of the next stage (s_waitcnt vmcnt,
 // exact: the loop issues no other vector memory operation), meets the other
 // waves at one barrier, reads the next operand group (GS k slices of 32) and

@@ -133,10 +133,11 @@ struct AppendArgs {
 };
 
 // Restore + reserve + append in one launch (no copy-on-write, no poisoning):
-// workgroup (0, 0) takes the crop of `ce` exactly as crop_kernel does, then the reservation pops of `e` from the stack it just pushed to
-// (tables, counts, lengths, top); the other workgroups copy the K/V of item
-// blockIdx.x - 1 and KV head blockIdx.y into block ids[item], which the host
-// mirror computed by the same steps.
+// workgroup (0, 0) takes the crop of `ce` exactly as crop_kernel does, then the
+// reservation pops of `e` from the stack it just pushed to (tables, counts,
+// lengths, top); the other workgroups copy the K/V of item blockIdx.x - 1 and KV
+// head blockIdx.y into block ids[item], which the host mirror computed by the same
+// steps.
 constexpr int kMaxFusedSeqs = 16;
 constexpr int kMaxFusedItems = 512;
 

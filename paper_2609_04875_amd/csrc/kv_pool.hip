@@ -187,6 +187,11 @@ __device__ inline uint8_t to_cache<uint16_t, uint8_t>(uint16_t x, float scale) {
   return e4m3_code(__uint_as_float((uint32_t)x << 16) / scale);
 }
 
+template <typename T>
+constexpr int kStagePad = sizeof(T) == 4 ? 4 : 8;   // elements; rows stay on chunk boundaries
+template <typename TI, typename T>
+constexpr int kAppendThreads = sizeof(TI) == sizeof(T) ? 64 : 256;
+
 // K/V of the tokens of one (sequence, logical block) item for one KV head,
 // bf16 pools, one wave: tokens p0 .. p0+nt-1 (block slots s0 .. s0+nt-1) from
 // the packed inputs (rows of n_kv_heads * D elements) into the block-head at
@@ -195,11 +200,6 @@ __device__ inline uint8_t to_cache<uint16_t, uint8_t>(uint16_t x, float scale) {
 // V is staged [slot][d] in LDS (rows padded to D + 8) and written back along d
 // rows: 16-byte runs of 8 slots when the span starts and ends on 8-slot
 // boundaries, else slot by slot (the partial first and last blocks).
-template <typename T>
-constexpr int kStagePad = sizeof(T) == 4 ? 4 : 8;   // elements; rows stay on chunk boundaries
-template <typename TI, typename T>
-constexpr int kAppendThreads = sizeof(TI) == sizeof(T) ? 64 : 256;
-
 template <int B, int D>
 __device__ inline void copy_block_head(const uint16_t* __restrict__ kin, const uint16_t* __restrict__ vin,
                                        int64_t row_stride, uint16_t* __restrict__ kc,

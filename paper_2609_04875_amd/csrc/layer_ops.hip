@@ -97,8 +97,9 @@ __global__ void __launch_bounds__(kThreads) rope_kernel(int64_t n_pairs, int32_t
 // this step costs (about a hundred instructions against four per pair for the
 // turn), so a workgroup forms a token's d/2 sines and cosines once, in LDS, and
 // turns all its heads with them, 8 pairs per thread and access: 2048 tokens x
-// 32 heads x 128: 23.4 -> 9.3 us, 8192 tokens 80.1 -> 23.2 us.  TPB tokens per workgroup: 4 fill the 256
-// threads of the angle step; few tokens take one each, for more workgroups.
+// 32 heads x 128: 23.4 -> 9.3 us, 8192 tokens 80.1 -> 23.2 us.  TPB tokens per
+// workgroup: 4 fill the 256 threads of the angle step; few tokens take one each,
+// for more workgroups.
 constexpr int kRopeHalf = 128;
 
 template <int TPB>
