@@ -369,7 +369,7 @@ def bench_stack(args):
         "roofline": {"bound": "mfma", "achieved": gflops / (gemm_ms * 1e-3) / 1e12,
                      "peak": PEAK_TFLOPS["bf16"], "unit": "TFLOP/s",
                      "frac": gflops / (gemm_ms * 1e-3) / 1e12 / PEAK_TFLOPS["bf16"], "traffic": None,
-                     "kernel": "gemm_bf16_kernel (x Wq, S x 8192 x 8192)", "kernel_ms": gemm_ms},
+                     "kernel": "pgsr_gemm_bf16 (x Wq, S x 8192 x 8192)", "kernel_ms": gemm_ms},
         "points": points,
     }
     print(json.dumps(result), flush=True)
@@ -578,7 +578,7 @@ def bench_decoder(args):
         "roofline": {"bound": "mfma", "achieved": gflops / (gemm_ms * 1e-3) / 1e12,
                      "peak": PEAK_TFLOPS["bf16"], "unit": "TFLOP/s",
                      "frac": gflops / (gemm_ms * 1e-3) / 1e12 / PEAK_TFLOPS["bf16"], "traffic": None,
-                     "kernel": "gemm_bf16_kernel (gate/up, S x 28672 x 4096)", "kernel_ms": gemm_ms},
+                     "kernel": "pgsr_gemm_bf16 (gate/up, S x 28672 x 4096)", "kernel_ms": gemm_ms},
         "points": points,
     }
     if not args.no_cpu_baseline:
